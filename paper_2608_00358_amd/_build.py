@@ -25,7 +25,8 @@ OBJDIR = os.path.join(PKG, "_build")
 ARCH = "gfx950"
 
 HOST_SOURCES = ["compiler.cpp", "validate.cpp"]
-HIP_SOURCES = ["executor.hip", "api.cpp"]
+EXECUTOR_SOURCES = ["executor_generic.hip", "executor_resident.hip", "executor.hip"]
+HIP_SOURCES = EXECUTOR_SOURCES + ["api.cpp"]
 
 HIPCC_FLAGS = [
     f"--offload-arch={ARCH}", "-O3", "-std=c++17", "-fPIC", "-Wall",
@@ -110,9 +111,10 @@ def build() -> str:
     """Compiles every source and links lib/libhccl.so. Always rebuilds."""
     os.makedirs(OBJDIR, exist_ok=True)
     os.makedirs(LIBDIR, exist_ok=True)
-    with cf.ThreadPoolExecutor(max_workers=4) as ex:
-        objs = list(ex.map(_compile, HOST_SOURCES + HIP_SOURCES))
-    check_device_code(os.path.join(OBJDIR, "executor.hip.o"))
+    with cf.ThreadPoolExecutor(max_workers=8) as ex:
+        objs = list(ex.map(_compile, HIP_SOURCES + HOST_SOURCES))
+    for src in EXECUTOR_SOURCES:
+        check_device_code(os.path.join(OBJDIR, src + ".o"))
     tmp = LIB + ".tmp"
     cmd = [_hipcc(), f"--offload-arch={ARCH}", "-shared", "-fPIC", "-o", tmp, *objs]
     res = subprocess.run(cmd, capture_output=True, text=True)
