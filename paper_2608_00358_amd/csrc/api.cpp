@@ -28,7 +28,7 @@
 
 namespace hccl {
 hipError_t launch_executor(const LaunchArgs& a, uint32_t blocks, int kind, hipStream_t stream);
-hipError_t launch_executor_inline(const InlineArgs& a, uint32_t blocks, int kind, hipStream_t stream);
+hipError_t launch_uniform(const UniformKernel& k, const UniformArgs& a, uint32_t blocks, hipStream_t stream);
 hipError_t launch_fill_u32(uint32_t* p, uint64_t n, uint32_t v, hipStream_t stream);
 hipError_t launch_signal(uint64_t* word, uint64_t value, const ErrorRecord* err, hipStream_t stream);
 hipError_t executor_occupancy(int kind, int* blocks_per_cu);
@@ -524,11 +524,17 @@ bool use_tickets(const hcclComm* c, const HostProgram& prog, bool triggered) {
     return triggered || trigger_pending(c->device) || resident_running(c->device);
 }
 
-// A program of one plain step without dependencies travels in the launch packet itself.
-bool inline_eligible(const hcclComm* c, const HostProgram& prog, bool triggered) {
-    const bool plain_step = prog.descs.size() == 1 && (prog.descs[0].op == OP_COPY || prog.descs[0].op == OP_REDUCE);
-    return c->inline_single_step && plain_step && (prog.flags & PF_HAS_DEPS) == 0 && c->dispatch_mode != 2 &&
-           !triggered && !c->cfg.trace;
+// Uniform phases travel in their launch packets: not where tickets, a trigger or a trace ask for
+// the tiles of the program image.
+bool inline_eligible(const hcclComm* c, bool triggered) {
+    return c->inline_single_step && c->dispatch_mode != 2 && !triggered && !c->cfg.trace;
+}
+
+// Whether nothing of a program needs its image.
+bool all_uniform(const HostProgram& prog) {
+    for (const UniformPhase& u : prog.uniform)
+        if (!u.ok) return false;
+    return !prog.uniform.empty();
 }
 
 // Trace buffer for `tiles` records (grown on demand; traced launches are a diagnostic mode).
@@ -550,28 +556,39 @@ hcclResult_t ensure_trace(hcclComm* c, uint64_t tiles) {
     return hcclSuccess;
 }
 
-hipError_t launch_inline_step(const HostProgram& prog, const LaunchArgs& a, uint32_t blocks, int kind, hipStream_t s) {
-    const HostDesc& d = prog.descs[0];
-    InlineArgs ia;
-    std::memset(&ia, 0, sizeof ia);
-    ia.nelem = d.nelem;
-    ia.tile_elems = prog.tile_elems;
-    ia.ntiles = prog.ntiles;
-    ia.nworkers = a.nworkers;
-    ia.op = d.op;
-    ia.redop = d.redop;
-    ia.nsrc = (uint32_t)d.srcs.size();
-    ia.ndst = (uint32_t)d.dsts.size();
-    ia.group = d.group;
-    ia.fold = d.fold;
-    ia.requant = d.requant ? 1u : 0u;
-    ia.es_first = dtype_size(d.srcs[0].dtype);
-    ia.es_rest = dtype_size(d.srcs.size() > 1 ? d.srcs[1].dtype : d.srcs[0].dtype);
-    ia.es_out = dtype_size(d.dsts[0].dtype);
-    ia.sig = reduce_signature(d.srcs[0].dtype, d.srcs.size() > 1 ? d.srcs[1].dtype : d.srcs[0].dtype, d.dsts[0].dtype);
-    for (size_t j = 0; j < d.srcs.size(); ++j) ia.src[j] = (uint64_t)(uintptr_t)a.bufs[d.srcs[j].buf] + d.srcs[j].offset;
-    for (size_t j = 0; j < d.dsts.size(); ++j) ia.dst[j] = (uint64_t)(uintptr_t)a.bufs[d.dsts[j].buf] + d.dsts[j].offset;
-    return launch_executor_inline(ia, blocks, kind, s);
+// Launches one uniform phase on the buffers `bufs`; the wavefronts of the launch go to `workers`.
+// One wavefront per tile, as for every launch in which no tile waits (see launch_shape).
+hipError_t launch_uniform_phase(const hcclComm* c, const UniformPhase& u, char* const* bufs, hipStream_t s, uint32_t& workers) {
+    UniformArgs a;
+    a.seg_elems = u.seg_elems;
+    a.last_elems = u.last_elems;
+    a.src_step = u.src_step;
+    a.dst_step = u.dst_step;
+    a.nseg = u.nseg;
+    a.tile_elems = u.tile_elems;
+    a.tiles_per_seg = (uint32_t)u.tiles_per_seg();
+    a.ntiles = (uint32_t)u.ntiles();
+    a.nsrc = u.nsrc();
+    a.ndst = u.ndst();
+    a.group = u.group;
+    a.flags = u.flags;
+    a.per_wave = u.per_wave;
+    // tiles are whole vectors, so the first element of every segment decides the alignment
+    uint64_t any = 0, differ = 0;
+    for (size_t i = 0; i < u.srcs.size(); ++i) any |= a.src[i] = (uint64_t)(uintptr_t)bufs[u.srcs[i].buf] + u.srcs[i].offset;
+    for (size_t i = 0; i < u.dsts.size(); ++i) {
+        any |= a.dst[i] = (uint64_t)(uintptr_t)bufs[u.dsts[i].buf] + u.dsts[i].offset;
+        differ |= a.dst[i] ^ a.dst[0];
+    }
+    if (u.nseg > 1) any |= u.src_step | u.dst_step;
+    if (any % 16 == 0) a.flags |= UF_ALIGNED;
+    if (differ % 16 == 0 || a.ndst == 1) a.flags |= UF_DST_AGREE;
+    const uint32_t wpb = (uint32_t)executor_waves_per_block();
+    workers = std::min<uint32_t>(a.ntiles, kMaxGridWorkers);
+    if (c->cfg.max_workers > 0) workers = std::min<uint32_t>(workers, (uint32_t)c->cfg.max_workers);
+    const uint32_t blocks = (workers + wpb - 1) / wpb;
+    a.nworkers = workers = blocks * wpb;
+    return launch_uniform(u.kernel, a, blocks, s);
 }
 
 // Program description for hccl_comm_last_program.
@@ -710,16 +727,10 @@ hcclResult_t run_packet(hcclComm* c, const std::vector<Call>& calls) {
     }
 
     uint32_t blocks = 0;
-    int kind = launch_shape(c, dp->prog, 0, a, nuser, s, blocks);
-    info.workers = a.nworkers;
+    int kind = 0;
     info.tickets = a.dynamic;
-
-    if (nph == 1 && inline_eligible(c, dp->prog, triggered)) {
-        info.inline_launch = 1;
-        hipError_t e = launch_inline_step(dp->prog, a, blocks, kind, s);
-        if (e != hipSuccess) return hip_fail(e, "inline executor launch");
-        return hcclSuccess;
-    }
+    const bool packed = inline_eligible(c, triggered);
+    info.inline_launch = packed && all_uniform(dp->prog) ? 1 : 0;
 
     // a program's counters serve one launch at a time, and the communicator's scratch one
     // program at a time: order such launches across streams. A captured launch is left out of
@@ -744,17 +755,20 @@ hcclResult_t run_packet(hcclComm* c, const std::vector<Call>& calls) {
     }
     hipError_t e = hipSuccess;
     for (uint32_t q = 0; q < nph; ++q) {
-        if (q > 0) {
-            // later phases follow the first on the stream: only the first waits for a trigger
-            a.wait_addr = nullptr;
+        if (q > 0) a.wait_addr = nullptr;  // later phases follow the first on the stream: only it waits for a trigger
+        if (packed && dp->prog.uniform[q].ok) {
+            e = launch_uniform_phase(c, dp->prog.uniform[q], a.bufs, s, a.nworkers);
+            if (e != hipSuccess) return hip_fail(e, "uniform launch");
+            hlog(c, 3, "launched phase %u of %u from the launch packet: %u wavefronts", q + 1, nph, a.nworkers);
+        } else {
             kind = launch_shape(c, dp->prog, q, a, nuser, s, blocks);
-            info.workers = std::max(info.workers, a.nworkers);
+            e = launch_executor(a, blocks, kind, s);
+            if (e != hipSuccess) return hip_fail(e, "executor launch");
+            hlog(c, 3, "launched phase %u of %u, kernel kind %d: %u workgroups, %u wavefronts, tiles %u..%u, %s dispatch%s",
+                 q + 1, nph, kind, blocks, a.nworkers, a.tile_begin, a.tile_end, a.dynamic ? "ticket" : "static",
+                 a.trace ? ", traced" : "");
         }
-        e = launch_executor(a, blocks, kind, s);
-        if (e != hipSuccess) return hip_fail(e, "executor launch");
-        hlog(c, 3, "launched phase %u of %u, kernel kind %d: %u workgroups, %u wavefronts, tiles %u..%u, %s dispatch%s",
-             q + 1, nph, kind, blocks, a.nworkers, a.tile_begin, a.tile_end, a.dynamic ? "ticket" : "static",
-             a.trace ? ", traced" : "");
+        info.workers = std::max(info.workers, a.nworkers);
     }
     if (signals) {
         e = launch_signal(trig.done_addr, trig.done_value, c->d_error, s);
@@ -1051,18 +1065,24 @@ hcclResult_t hccl_allreduce_noalloc(hcclComm_t comm, const void* const* sendbufs
     comm->last.workers = a.nworkers;
     comm->last.tickets = a.dynamic;
     hipError_t e;
-    if (hp->nphase() == 1 && inline_eligible(comm, *hp, false)) {
+    if (inline_eligible(comm, false) && all_uniform(*hp)) {
         comm->last.inline_launch = 1;
-        e = launch_inline_step(*hp, a, blocks, kind, st);
-        if (e != hipSuccess) return hip_fail(e, "inline executor launch");
+        for (uint32_t q = 0; q < hp->nphase(); ++q) {
+            uint32_t workers = 0;
+            e = launch_uniform_phase(comm, hp->uniform[q], a.bufs, st, workers);
+            if (e != hipSuccess) return hip_fail(e, "uniform launch");
+            comm->last.workers = q ? std::max(comm->last.workers, workers) : workers;
+        }
         return hcclSuccess;
     }
-    // the image goes in with a copy on the stream, the counters start from zero (a fill kernel),
-    // the partials need no clearing: every one is written before it is read
+    // the image goes in with a copy on the stream, the counters that the launch reads start from
+    // zero (a fill kernel), the partials need no clearing: every one is written before it is read
     e = hipMemcpyAsync(ws, hp->image.data(), hp->image.size(), hipMemcpyHostToDevice, st);
     if (e != hipSuccess) return hip_fail(e, "program copy into the static workspace");
-    e = launch_fill_u32(a.state, hp->nstate, 0u, st);
-    if (e != hipSuccess) return hip_fail(e, "counter clear in the static workspace");
+    if ((hp->flags & PF_HAS_DEPS) != 0 || a.dynamic) {
+        e = launch_fill_u32(a.state, hp->nstate, 0u, st);
+        if (e != hipSuccess) return hip_fail(e, "counter clear in the static workspace");
+    }
     for (uint32_t q = 0; q < hp->nphase(); ++q) {
         if (q > 0) {
             kind = launch_shape(comm, *hp, q, a, 2u * (uint32_t)P, st, blocks);

@@ -1013,6 +1013,221 @@ bool merge(std::vector<HostProgram>& parts, const std::vector<CollectiveSpec>& s
     return true;
 }
 
+// ---------------------------------------------------------------------- uniform phases
+namespace {
+
+// Tiles of a uniform phase, measured on MI355X with three sets of buffers in turn (so that a call
+// does not find its own inputs in the last-level cache). Bytes per tile are those of one source.
+//  * Reductions: 2 KiB, two vectors per lane and source; 4 KiB from 1 GiB moved on; 1 KiB for the
+//    binary tree, which takes one vector per lane. 1 / 2 / 4 KiB: 8-rank reduce-scatter of 64 MiB
+//    bf16 29.2 / 27.3 / 28.6 us, ragged 31.8 / 30.7 / 36.9, of 1 GiB 404 / 415 / 405; all-reduce
+//    of 8 x 16 MiB bf16 58.1 / 52.9 / 58.8; 16-rank halving reduce-scatter of 8 MiB fp16 23.9 /
+//    25.2 / 28.1. (8 and 16 KiB: the 1 GiB one 455 and 473 us.)
+//  * Copies: 4 KiB. 2 / 4 / 8 KiB: all-gather of 8 x 8 MiB 95.5 / 86.4 / 97, of 2 x 64 MiB
+//    67.3 / 67.7 / 75.3, of 8 x 104 KB 6.1 / 5.1 / 5.4.
+//  * Small phases are cut further, down to one vector per lane, to give more wavefronts work.
+constexpr uint64_t kUniformReduceBytes = 2048;
+constexpr uint64_t kUniformLargeReduceBytes = 4096;
+constexpr uint64_t kUniformLargeMoved = 1ull << 30;
+constexpr uint64_t kUniformCopyBytes = 4096;
+constexpr uint64_t kUniformCopyTiles = 256;
+constexpr uint64_t kUniformStepBytes = kWaveSize * 16;
+// Destinations that one wavefront of a copy writes: all of them, its tile loaded once; four, the
+// others left to its neighbours, while that makes fewer than this many wavefronts. One / four /
+// all: all-gather of 8 x 8 MiB 96.7 / 96.5 / 86.4 us; of 8 x 1.2 MB 15.9 / 15.5 / 16.8; of
+// 32 x 13.8 KB 6.3 / 5.5 / 17.3; of 64 x 9 KB 8.9 / 7.9 / 24.0.
+constexpr uint32_t kUniformFewDsts = 4;
+constexpr uint64_t kUniformFewWaves = 16384;
+// A reduction that moves no more than this finds its inputs in the caches, where the producer left
+// them: ordinary loads (all-reduce of 8 x 64 KiB 6.0 -> 4.9 us back to back); beyond it the
+// non-temporal ones are as good or better (of 8 x 2 MiB 7.6 / 6.8, of 16 x 8 MiB 26.4 / 23.9, the
+// 1 GiB reduce-scatter 435 / 405). Results are stored non-temporally at every size (all-reduce of
+// 4 x 4 MiB: ordinary stores 7.8, non-temporal 6.9), unless a later phase of the program reads them.
+constexpr uint64_t kUniformCachedBytes = 8ull << 20;
+
+void uniform_tile(UniformPhase& u, uint64_t elems) {
+    const uint64_t es = dtype_size(u.kernel.dtype);
+    const uint64_t moved = elems * es * (u.nsrc() + u.ndst());
+    uint64_t bytes = kUniformCopyBytes, sets = 1, want = kUniformCopyTiles;
+    if (u.kernel.op == OP_REDUCE) {
+        bytes = u.kernel.fold == FOLD_PAIRWISE ? kUniformStepBytes
+              : moved >= kUniformLargeMoved && u.nsrc() < kSplitMinSources ? kUniformLargeReduceBytes : kUniformReduceBytes;
+        want = kSmallTargetTiles;
+    } else {
+        const uint64_t few = (u.ndst() + kUniformFewDsts - 1) / kUniformFewDsts;
+        const bool split = (elems * es + bytes - 1) / bytes * few < kUniformFewWaves;
+        u.per_wave = split ? std::min(kUniformFewDsts, u.ndst()) : u.ndst();
+        sets = split ? few : 1;
+    }
+    while (bytes > kUniformStepBytes && elems * es / bytes * sets < want) bytes /= 2;
+    u.tile_elems = (uint32_t)(bytes / es);
+}
+
+bool same_bufs(const std::vector<Operand>& a, const std::vector<Operand>& b) {
+    if (a.size() != b.size()) return false;
+    for (size_t i = 0; i < a.size(); ++i)
+        if (a[i].buf != b[i].buf) return false;
+    return true;
+}
+
+// The uniform form of the steps [d0, d1) of one phase, none of which waits for another. `tile`
+// is the tile size of a configured tile_bytes (0: chosen here), which the caller asked for step
+// by step: then only a single step has this form. `reread`: a later phase reads the results.
+UniformPhase find_uniform(const std::vector<HostDesc>& all, uint32_t d0, uint32_t d1, uint32_t tile, bool reread) {
+    UniformPhase u;
+    if (d0 == d1 || (tile && d1 - d0 != 1)) return u;
+    const HostDesc& f = all[d0];
+    if (f.op != OP_COPY && f.op != OP_REDUCE) return u;
+    if (f.srcs.empty() || f.dsts.empty()) return u;
+    const uint32_t dt = f.srcs[0].dtype;
+    const uint64_t es = dtype_size(dt);
+    std::vector<HostDesc> steps;
+    for (uint32_t i = d0; i < d1; ++i) {
+        const HostDesc& d = all[i];
+        if (d.op != f.op || d.redop != f.redop || d.group != f.group || d.fold != f.fold || d.requant != f.requant ||
+            !d.deps.empty() || d.nelem == 0 || d.srcs.size() != f.srcs.size() || d.dsts.size() != f.dsts.size())
+            return u;
+        for (const auto* list : {&d.srcs, &d.dsts})
+            for (const Operand& o : *list)
+                if (o.dtype != dt) return u;
+        steps.push_back(d);
+    }
+    for (HostDesc& d : steps)  // the order of a step's destinations is free
+        std::sort(d.dsts.begin(), d.dsts.end(), [](const Operand& a, const Operand& b) { return a.buf < b.buf; });
+    // join the steps that continue one another in every operand
+    auto bufs_less = [](const std::vector<Operand>& a, const std::vector<Operand>& b) {
+        return std::lexicographical_compare(a.begin(), a.end(), b.begin(), b.end(),
+                                            [](const Operand& x, const Operand& y) { return x.buf < y.buf; });
+    };
+    std::stable_sort(steps.begin(), steps.end(), [&](const HostDesc& a, const HostDesc& b) {
+        if (!same_bufs(a.srcs, b.srcs)) return bufs_less(a.srcs, b.srcs);
+        if (!same_bufs(a.dsts, b.dsts)) return bufs_less(a.dsts, b.dsts);
+        return a.dsts[0].offset < b.dsts[0].offset;
+    });
+    std::vector<HostDesc> segs;
+    for (HostDesc& d : steps) {
+        bool joins = !segs.empty() && same_bufs(segs.back().srcs, d.srcs) && same_bufs(segs.back().dsts, d.dsts);
+        if (joins) {
+            const HostDesc& p = segs.back();
+            for (size_t k = 0; k < d.srcs.size(); ++k) joins &= d.srcs[k].offset == p.srcs[k].offset + p.nelem * es;
+            for (size_t k = 0; k < d.dsts.size(); ++k) joins &= d.dsts[k].offset == p.dsts[k].offset + p.nelem * es;
+        }
+        if (joins) segs.back().nelem += d.nelem;
+        else segs.push_back(std::move(d));
+        if (segs.size() > (size_t)kMaxOperands) return u;
+    }
+    std::stable_sort(segs.begin(), segs.end(), [](const HostDesc& a, const HostDesc& b) {
+        if (a.dsts[0].offset != b.dsts[0].offset) return a.dsts[0].offset < b.dsts[0].offset;
+        if (a.srcs[0].offset != b.srcs[0].offset) return a.srcs[0].offset < b.srcs[0].offset;
+        return a.srcs[0].buf < b.srcs[0].buf;
+    });
+    const HostDesc& s0 = segs[0];
+    const uint32_t n = (uint32_t)segs.size();
+    for (uint32_t g = 1; g < n; ++g)
+        if (g + 1 < n ? segs[g].nelem != s0.nelem : segs[g].nelem > s0.nelem) return u;
+
+    // one list for every segment, at a constant step?
+    auto shared = [&](std::vector<Operand> HostDesc::*list, uint64_t& step) {
+        const auto& base = s0.*list;
+        step = n > 1 ? (segs[1].*list)[0].offset - base[0].offset : 0;
+        for (uint32_t g = 1; g < n; ++g) {
+            if (!same_bufs(segs[g].*list, base)) return false;
+            for (size_t k = 0; k < base.size(); ++k)
+                if ((segs[g].*list)[k].offset != base[k].offset + g * step) return false;
+        }
+        return true;
+    };
+    // the sources of segment g are those of one list from its place g + 1 on (ring order)?
+    auto rotated = [&](uint64_t step, std::vector<Operand>& base) {
+        const uint32_t m = (uint32_t)s0.srcs.size();
+        base.resize(m);
+        for (uint32_t k = 0; k < m; ++k) base[(k + 1) % m] = s0.srcs[k];
+        for (uint32_t g = 0; g < n; ++g)
+            for (uint32_t k = 0; k < m; ++k) {
+                const Operand &o = base[(k + g + 1) % m], &x = segs[g].srcs[k];
+                if (x.buf != o.buf || x.offset != o.offset + g * step) return false;
+            }
+        return n <= m;
+    };
+    // ... or those of segment 0 with the bits of g, in reverse, flipped in their place (halving order)?
+    auto flipped = [&](uint64_t step) {
+        const uint32_t m = (uint32_t)s0.srcs.size();
+        if ((m & (m - 1)) != 0 || n > m) return false;
+        for (uint32_t g = 0; g < n; ++g) {
+            uint32_t rev = 0;
+            for (uint32_t b = 1, t = m >> 1; b < m; b <<= 1, t >>= 1)
+                if (g & b) rev |= t;
+            for (uint32_t k = 0; k < m; ++k) {
+                const Operand &o = s0.srcs[k ^ rev], &x = segs[g].srcs[k];
+                if (x.buf != o.buf || x.offset != o.offset + g * step) return false;
+            }
+        }
+        return true;
+    };
+    std::vector<Operand> base;
+    if (shared(&HostDesc::srcs, u.src_step)) {
+        u.srcs = s0.srcs;
+    } else if (s0.srcs.size() == 1) {
+        u.flags |= UF_SRC_PER_SEG;
+        u.src_step = 0;
+        for (const HostDesc& d : segs) u.srcs.push_back(d.srcs[0]);
+    } else if (rotated(u.src_step = segs[1].srcs[0].offset - s0.srcs[0].offset, base)) {
+        u.flags |= UF_ROTATE;
+        u.srcs = base;
+    } else if (flipped(u.src_step)) {
+        u.flags |= UF_FLIP;
+        u.srcs = s0.srcs;
+    } else {
+        return u;
+    }
+    if (shared(&HostDesc::dsts, u.dst_step)) {
+        u.dsts = s0.dsts;
+    } else if (s0.dsts.size() == 1) {
+        u.flags |= UF_DST_PER_SEG;
+        u.dst_step = 0;
+        for (const HostDesc& d : segs) u.dsts.push_back(d.dsts[0]);
+    } else if (f.op == OP_COPY && s0.dsts.size() < (size_t)kMaxOperands) {
+        // copies of one location of every buffer but the source's own (the results of a two-level
+        // all-reduce): the list of all of them; a wavefront leaves out the destination that is
+        // its source
+        auto with_source = [](const HostDesc& d) {
+            std::vector<Operand> v = d.dsts;
+            v.push_back(d.srcs[0]);
+            std::sort(v.begin(), v.end(), [](const Operand& a, const Operand& b) { return a.buf < b.buf; });
+            return v;
+        };
+        u.dsts = with_source(s0);
+        u.dst_step = with_source(segs[1])[0].offset - u.dsts[0].offset;
+        for (uint32_t g = 0; g < n; ++g) {
+            const std::vector<Operand> v = with_source(segs[g]);
+            if (!same_bufs(v, u.dsts)) return u;
+            for (size_t k = 0; k < v.size(); ++k)
+                if (v[k].offset != u.dsts[k].offset + g * u.dst_step || (k && v[k].buf == v[k - 1].buf)) return u;
+        }
+    } else {
+        return u;
+    }
+    u.group = f.group;
+    u.nseg = n;
+    u.seg_elems = s0.nelem;
+    u.last_elems = segs[n - 1].nelem;
+    uint64_t total = 0;
+    for (const HostDesc& d : segs) total += d.nelem;
+    u.kernel = {f.op, (uint8_t)dt, f.redop, (uint8_t)f.fold, f.requant, 0};
+    // (a maximum, a minimum and a wrapping sum do not depend on how their list is bracketed)
+    if (f.op == OP_REDUCE && (f.redop != RO_SUM || dt == DT_INT32)) u.kernel.fold = FOLD_LIST, u.group = 0;
+    if (f.op == OP_REDUCE && (f.redop != RO_SUM || dt == DT_INT32 || dt == DT_FP32)) u.kernel.requant = false;
+    if (f.op == OP_REDUCE && reread) u.kernel.mem = MEM_STORE;
+    else if (f.op == OP_REDUCE && total * es * (u.nsrc() + u.ndst()) <= kUniformCachedBytes) u.kernel.mem = MEM_LOAD;
+    u.per_wave = 1;
+    if (tile) u.tile_elems = tile;
+    else uniform_tile(u, total);
+    u.ok = u.ntiles() < (1ull << 31);
+    return u;
+}
+
+}  // namespace
+
 // ---------------------------------------------------------------------------- packing
 bool finalize(HostProgram& p, uint32_t tile_bytes, std::string& err) {
     // compact
@@ -1233,6 +1448,7 @@ bool finalize(HostProgram& p, uint32_t tile_bytes, std::string& err) {
     p.phase_tile.assign(1, 0);
     p.phase_kind.clear();
     p.phase_xcd.clear();
+    p.uniform.clear();
     for (uint32_t q = 0, i = 0; q < nphase; ++q) {
         const uint32_t d0 = i;
         while (i < nd && p.desc_phase[i] == q) ++i;
@@ -1242,6 +1458,8 @@ bool finalize(HostProgram& p, uint32_t tile_bytes, std::string& err) {
         bool wide = i > d0;
         for (uint32_t k = d0; k < i; ++k) wide &= out[k].op == OP_REDUCE && out[k].nsrc >= kSplitMinSources;
         p.phase_xcd.push_back(wide ? 1 : 0);
+        p.uniform.push_back(has_deps ? UniformPhase() : find_uniform(p.descs, d0, i, tile_bytes ? p.tile_elems : 0, q + 1 < nphase));
+        if (wide) p.uniform.back().flags |= UF_XCD;
         p.phase_tile.push_back(i < nd ? out[i].tile0 : p.ntiles);
     }
 

@@ -79,6 +79,29 @@ struct HostDesc {
     uint32_t aux = 0;            // OP_DYN_*: index into HostProgram::aux
 };
 
+// A phase whose steps are one fold or copy over equal segments (see UniformArgs): chunks that
+// continue one another are joined again, and what is left differs only by a constant step in its
+// addresses, by which buffer it reads or writes, or by a rotation of its source list.
+struct UniformPhase {
+    bool ok = false;
+    UniformKernel kernel{};
+    uint32_t group = 0;
+    uint32_t nseg = 0;
+    uint64_t seg_elems = 0, last_elems = 0;
+    uint64_t src_step = 0, dst_step = 0;  // bytes
+    uint32_t flags = 0;                   // UF_SRC_PER_SEG, UF_DST_PER_SEG, UF_ROTATE, UF_XCD
+    uint32_t tile_elems = 0;
+    uint32_t per_wave = 0;
+    std::vector<Operand> srcs, dsts;      // of segment 0, or one per segment
+    uint32_t nsrc() const { return flags & UF_SRC_PER_SEG ? 1u : (uint32_t)srcs.size(); }
+    uint32_t ndst() const { return flags & UF_DST_PER_SEG ? 1u : (uint32_t)dsts.size(); }
+    uint64_t tiles_per_seg() const { return (seg_elems + tile_elems - 1) / tile_elems; }
+    uint64_t ntiles() const {
+        const uint64_t t = (nseg - 1) * tiles_per_seg() + (last_elems + tile_elems - 1) / tile_elems;
+        return kernel.op == OP_COPY ? t * ((ndst() + per_wave - 1) / per_wave) : t;
+    }
+};
+
 struct HostProgram {
     int P = 0;
     int algo = ALGO_DIRECT;      // schedule actually lowered
@@ -109,6 +132,7 @@ struct HostProgram {
     std::vector<uint32_t> phase_tile;
     std::vector<int> phase_kind;
     std::vector<uint8_t> phase_xcd;  // 1 = the phase's wavefronts are numbered XCD by XCD
+    std::vector<UniformPhase> uniform;  // one per phase
     uint32_t nphase() const { return phase_kind.empty() ? 1u : (uint32_t)phase_kind.size(); }
 };
 

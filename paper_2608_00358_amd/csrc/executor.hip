@@ -40,25 +40,7 @@ __global__ void hccl_fill_u32(uint32_t* p, uint64_t n, uint32_t v) {
 
 // the generic kernel (executor_generic.hip)
 hipError_t launch_generic(const LaunchArgs& a, uint32_t blocks, hipStream_t stream);
-hipError_t launch_generic_inline(const InlineArgs& a, uint32_t blocks, hipStream_t stream);
 hipError_t generic_occupancy(int* blocks_per_cu);
-
-hipError_t launch_executor_inline(const InlineArgs& a, uint32_t blocks, int kind, hipStream_t stream) {
-    switch (kind) {
-        case SIG_BF16: hipLaunchKernelGGL(hccl_executor_inline<SIG_BF16>, dim3(blocks), dim3(kBlockThreads), 0, stream, a); break;
-        case SIG_FP16: hipLaunchKernelGGL(hccl_executor_inline<SIG_FP16>, dim3(blocks), dim3(kBlockThreads), 0, stream, a); break;
-        case SIG_FP32: hipLaunchKernelGGL(hccl_executor_inline<SIG_FP32>, dim3(blocks), dim3(kBlockThreads), 0, stream, a); break;
-        case SIG_INT32: hipLaunchKernelGGL(hccl_executor_inline<SIG_INT32>, dim3(blocks), dim3(kBlockThreads), 0, stream, a); break;
-        case kKindCopyOnly:
-            hipLaunchKernelGGL(hccl_executor_inline<kKindCopyOnly>, dim3(blocks), dim3(kBlockThreads), 0, stream, a);
-            break;
-        case kKindCopyAligned:
-            hipLaunchKernelGGL(hccl_executor_inline<kKindCopyAligned>, dim3(blocks), dim3(kBlockThreads), 0, stream, a);
-            break;
-        default: return launch_generic_inline(a, blocks, stream);
-    }
-    return hipGetLastError();
-}
 
 int executor_block_threads() { return kBlockThreads; }
 

@@ -1438,33 +1438,6 @@ hccl_executor(LaunchArgs a) {
     }
 }
 
-// A program of one step needs no device image: its step travels inside the launch packet
-// with every operand already resolved to an address (the analogue of the express doorbell,
-// where the work request itself is the doorbell write and nothing is fetched first).
-template <int KIND>
-__global__ void __launch_bounds__(kBlockThreads) hccl_executor_inline(InlineArgs a) {
-    const uint32_t lane = __lane_id();
-    const uint32_t wave = uni(blockIdx.x * kWavesPerBlock + (threadIdx.x / kWaveSize));
-    const char* kargs = (const char*)__builtin_amdgcn_kernarg_segment_ptr();
-    const uint64_t* srcs = (const uint64_t*)(kargs + offsetof(InlineArgs, src));
-    const uint64_t* dsts = (const uint64_t*)(kargs + offsetof(InlineArgs, dst));
-    TileOps ops;
-    ops.nsrc = a.nsrc;
-    ops.ndst = a.ndst;
-    ops.group = a.group;
-    ops.fold = a.fold;
-    ops.requant = a.requant;
-    const uint64_t te = a.tile_elems;
-    for (uint32_t t = wave; t < a.ntiles; t += a.nworkers) {
-        const uint64_t e0 = (uint64_t)t * te;
-        const uint32_t n = (uint32_t)((a.nelem - e0 < te) ? (a.nelem - e0) : te);
-        ops.src = lane < ops.nsrc ? srcs[lane] + e0 * (lane == 0 ? a.es_first : a.es_rest) : 0;
-        ops.dst = lane < ops.ndst ? dsts[lane] + e0 * a.es_out : 0;
-        const bool misaligned = (lane < ops.nsrc && (ops.src & 15u)) || (lane < ops.ndst && (ops.dst & 15u));
-        exec_tile<KIND>(a.op, a.sig, a.redop, a.es_first, ops, n, __ballot(misaligned) == 0ull, lane);
-    }
-}
-
 }  // namespace
 
 }  // namespace hccl

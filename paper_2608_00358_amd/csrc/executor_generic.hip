@@ -9,11 +9,6 @@ hipError_t launch_generic(const LaunchArgs& a, uint32_t blocks, hipStream_t stre
     return hipGetLastError();
 }
 
-hipError_t launch_generic_inline(const InlineArgs& a, uint32_t blocks, hipStream_t stream) {
-    hipLaunchKernelGGL(hccl_executor_inline<kKindGeneric>, dim3(blocks), dim3(kBlockThreads), 0, stream, a);
-    return hipGetLastError();
-}
-
 hipError_t generic_occupancy(int* blocks_per_cu) {
     return hipOccupancyMaxActiveBlocksPerMultiprocessor(blocks_per_cu, hccl_executor<kKindGeneric>, kBlockThreads, 0);
 }

@@ -1,0 +1,460 @@
+// executor_uniform.hip -- kernels of the uniform phases (UniformArgs): one fold or one copy over
+// equal segments, described by the launch packet alone.
+//
+// A wavefront of the descriptor executor finds its tile through the program image: header, tile
+// table, descriptor, operands, buffer table, each a dependent read of memory. Here tile number and
+// kernel arguments give every address by arithmetic, the pointers in scalar registers. Every kernel
+// is compiled for one type, one operator and one fold, with as many loads in flight as that allows.
+#include "executor_device.h"
+
+namespace hccl {
+
+namespace {
+
+enum Mode { M_SUM, M_MINMAX, M_REQ };  // M_REQ: SUM, every partial rounded to the element type
+
+constexpr int kBatch = 8;   // sources whose loads are in flight together
+constexpr int kUnroll = 2;  // 16-byte vectors per lane and source in flight
+
+// The operand lists in the kernel-argument segment: uniform indexes make scalar loads.
+typedef const __attribute__((address_space(4))) uint64_t* ArgList;
+
+template <int T> constexpr int kVec = 16 / DtInfo<T>::size;  // elements of a 16-byte vector
+
+typedef float f32x2 __attribute__((ext_vector_type(2)));
+typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+
+// Two fp32 -> bf16 in one instruction (v_cvt_pk_bf16_f32): the same bits as bf16_bits for all 2^32
+// inputs, NaNs included.
+__device__ __forceinline__ uint32_t bf16_pair(float a, float b) {
+    const f32x2 v = {a, b};
+    return __builtin_bit_cast(uint32_t, __builtin_convertvector(v, bf16x2));
+}
+
+template <int T, typename A>
+__device__ __forceinline__ void widen(const u32x4& r, A (&x)[kVec<T>]) {
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        if constexpr (T == DT_BF16) {
+            x[2 * i] = bf16_lo(r[i]);
+            x[2 * i + 1] = bf16_hi(r[i]);
+        } else if constexpr (T == DT_FP16) {
+            x[2 * i] = f16_lo(r[i]);
+            x[2 * i + 1] = f16_hi(r[i]);
+        } else if constexpr (T == DT_FP32) {
+            x[i] = __uint_as_float(r[i]);
+        } else {
+            x[i] = (int32_t)r[i];
+        }
+    }
+}
+
+template <int T, typename A>
+__device__ __forceinline__ u32x4 narrow(const A (&x)[kVec<T>]) {
+    u32x4 w;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        if constexpr (T == DT_BF16) w[i] = bf16_pair(x[2 * i], x[2 * i + 1]);
+        else if constexpr (T == DT_FP16) w[i] = f16_bits(x[2 * i]) | (f16_bits(x[2 * i + 1]) << 16);
+        else if constexpr (T == DT_FP32) w[i] = __float_as_uint(x[i]);
+        else w[i] = (uint32_t)x[i];
+    }
+    return w;
+}
+
+// a = a op x, element by element; OPR is RO_SUM, RO_MAX or RO_MIN.
+template <int T, int OPR, bool REQ, typename A>
+__device__ __forceinline__ void combine(A (&a)[kVec<T>], const A (&x)[kVec<T>]) {
+#pragma unroll
+    for (int i = 0; i < kVec<T>; ++i) a[i] = comb<OPR>(a[i], x[i]);
+    if constexpr (REQ) widen<T, A>(narrow<T, A>(a), a);
+}
+
+// The fold of one tile's segment: where its sources and destinations are.
+struct Fold1 {
+    ArgList src, dst;
+    uint64_t src_off, dst_off;  // bytes from a list entry to element 0 of the tile
+    uint32_t nsrc, ndst, group;
+    uint32_t rot, flip;         // source i of the fold is entry (i + rot) mod nsrc, or i ^ flip
+    __device__ __forceinline__ const char* source(uint32_t i) const {
+        uint32_t k = i + rot;
+        if (k >= nsrc) k -= nsrc;
+        return (const char*)(src[k ^ flip] + src_off);
+    }
+    __device__ __forceinline__ char* dest(uint32_t j) const { return (char*)(dst[j] + dst_off); }
+};
+
+// MEM: which accesses are ordinary (MemFlags); the others are non-temporal. SHIFT: addresses aligned only to the element.
+template <int T, bool SHIFT, int MEM>
+__device__ __forceinline__ u32x4 load_vec(const char* p) {
+    if constexpr (SHIFT) return vld_shifted<DtInfo<T>::size>(p);
+    else if constexpr (MEM & MEM_LOAD) return *gp<u32x4>(p);
+    else return __builtin_nontemporal_load(gp<u32x4>(p));
+}
+template <int MEM>
+__device__ __forceinline__ void store_vec(char* p, u32x4 v) {
+    if constexpr (MEM & MEM_STORE) *gp<u32x4>(p) = v;
+    else __builtin_nontemporal_store(v, gp<u32x4>(p));
+}
+
+// Fold in list order of U vectors per lane, the first at byte `at` of the tile, 1 KiB apart.
+// The loads of kBatch sources are all issued before the first of them is folded: one memory round
+// trip for 8 sources.
+template <int T, int OPR, bool REQ, int U, bool SHIFT, int MEM, bool GROUPED>
+__device__ __forceinline__ void fold_list(const Fold1& f, uint32_t at) {
+    typedef typename DtInfo<T>::acc A;
+    A acc[U][kVec<T>], tot[GROUPED ? U : 1][kVec<T>];
+    const uint32_t L = GROUPED ? f.group : f.nsrc;
+    for (uint32_t g0 = 0; g0 < f.nsrc; g0 += L) {
+        const uint32_t end = (!GROUPED || g0 + L > f.nsrc) ? f.nsrc : g0 + L;
+        for (uint32_t s = g0; s < end; s += kBatch) {
+            u32x4 r[kBatch][U];
+#pragma unroll
+            for (int j = 0; j < kBatch; ++j) {
+                if (s + j < end) {
+                    const char* b = f.source(s + j);
+#pragma unroll
+                    for (int u = 0; u < U; ++u) r[j][u] = load_vec<T, SHIFT, MEM>(b + (at + u * 1024u));
+                }
+            }
+#pragma unroll
+            for (int j = 0; j < kBatch; ++j) {
+                if (s + j < end) {
+#pragma unroll
+                    for (int u = 0; u < U; ++u) {
+                        A x[kVec<T>];
+                        widen<T, A>(r[j][u], x);
+                        if (j == 0 && s == g0) {
+#pragma unroll
+                            for (int i = 0; i < kVec<T>; ++i) acc[u][i] = x[i];
+                        } else {
+                            combine<T, OPR, REQ, A>(acc[u], x);
+                        }
+                    }
+                }
+            }
+        }
+        if constexpr (GROUPED) {
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                if (g0 == 0) {
+#pragma unroll
+                    for (int i = 0; i < kVec<T>; ++i) tot[u][i] = acc[u][i];
+                } else {
+                    combine<T, OPR, REQ, A>(tot[u], acc[u]);
+                }
+            }
+        }
+    }
+    u32x4 w[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) w[u] = narrow<T, A>(GROUPED ? tot[GROUPED ? u : 0] : acc[u]);
+    for (uint32_t d = 0; d < f.ndst; ++d) {
+        char* b = f.dest(d);
+#pragma unroll
+        for (int u = 0; u < U; ++u) store_vec<MEM>(b + (at + u * 1024u), w[u]);
+    }
+}
+
+// Fold as a complete binary tree over the list: eight sources at a time make one subtree, and the
+// subtrees before the current one wait on a stack of three levels (64 sources).
+template <int T, bool REQ, bool SHIFT, int MEM>
+__device__ __forceinline__ void fold_tree(const Fold1& f, uint32_t at) {
+    typedef float A;
+    constexpr int V = kVec<T>;
+    A stk[3][V], v[V];
+    const uint32_t nb = (f.nsrc + 7) / 8;
+    for (uint32_t b = 0; b < nb; ++b) {
+        u32x4 r[8];
+#pragma unroll
+        for (int j = 0; j < 8; ++j)
+            if (8 * b + j < f.nsrc) r[j] = load_vec<T, SHIFT, MEM>(f.source(8 * b + j) + at);
+        A p[3][V], x[V];
+        // pairs, pairs of pairs, and those two, as far as there are sources
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            if ((uint32_t)(2 * q) < f.nsrc) {
+                A(&t)[V] = (q & 1) ? p[2] : p[q / 2];
+                widen<T, A>(r[2 * q], t);
+                if ((uint32_t)(2 * q + 1) < f.nsrc) {
+                    widen<T, A>(r[2 * q + 1], x);
+                    combine<T, RO_SUM, REQ, A>(t, x);
+                }
+                if (q & 1) combine<T, RO_SUM, REQ, A>(p[q / 2], p[2]);
+            }
+        }
+        if (f.nsrc > 4) combine<T, RO_SUM, REQ, A>(p[0], p[1]);
+#pragma unroll
+        for (int i = 0; i < V; ++i) v[i] = p[0][i];
+        bool open = true;
+#pragma unroll
+        for (int l = 0; l < 3; ++l) {
+            if (open && (2u << l) <= nb) {
+                if ((b >> l) & 1u) {
+                    combine<T, RO_SUM, REQ, A>(stk[l], v);
+#pragma unroll
+                    for (int i = 0; i < V; ++i) v[i] = stk[l][i];
+                } else {
+#pragma unroll
+                    for (int i = 0; i < V; ++i) stk[l][i] = v[i];
+                    open = false;
+                }
+            }
+        }
+    }
+    const u32x4 w = narrow<T, A>(v);
+    for (uint32_t d = 0; d < f.ndst; ++d) store_vec<MEM>(f.dest(d) + at, w);
+}
+
+// Elements [first, first + count) of the tile, one per lane (heads and tails of misaligned tiles,
+// tiles whose destinations disagree modulo 16). The tree's stack has six levels here.
+template <int T, int OPR, bool REQ, bool TREE>
+__device__ __forceinline__ void fold_elems(const Fold1& f, uint32_t first, uint32_t count, uint32_t lane) {
+    typedef typename DtInfo<T>::acc A;
+    constexpr uint32_t S = DtInfo<T>::size;
+    auto round = [](A v) { return requant<T, REQ>(v); };
+    for (uint32_t e = first + lane; e < first + count; e += kWaveSize) {
+        A acc = A(0), tot = A(0), stk[TREE ? 6 : 1];
+        const uint32_t L = f.group ? f.group : f.nsrc;
+        uint32_t left = 0;  // sources of the group still to come
+        for (uint32_t s = 0; s < f.nsrc; s += kBatch) {
+            A x[kBatch];
+#pragma unroll
+            for (int j = 0; j < kBatch; ++j)
+                if (s + j < f.nsrc) x[j] = load1<T, A>(f.source(s + j) + (uint64_t)e * S);
+#pragma unroll
+            for (int j = 0; j < kBatch; ++j) {
+                if (s + j >= f.nsrc) continue;
+                if constexpr (TREE) {
+                    bool open = true;
+                    acc = x[j];
+#pragma unroll
+                    for (int l = 0; l < 6; ++l) {
+                        if (open && (2u << l) <= f.nsrc) {
+                            if (((s + j) >> l) & 1u) acc = round(comb<OPR>(stk[l], acc));
+                            else stk[l] = acc, open = false;
+                        }
+                    }
+                } else if (left == 0) {  // the first of a group: what was folded so far joins the total
+                    if (s + j == L) tot = acc;
+                    else if (s + j > L) tot = round(comb<OPR>(tot, acc));
+                    acc = x[j];
+                    left = L - 1;
+                } else {
+                    acc = round(comb<OPR>(acc, x[j]));
+                    --left;
+                }
+            }
+        }
+        if (!TREE && L < f.nsrc) acc = round(comb<OPR>(tot, acc));
+        for (uint32_t d = 0; d < f.ndst; ++d) store1<T, A>(f.dest(d) + (uint64_t)e * S, acc);
+    }
+}
+
+// Elements [first, n) of the tile in vectors (its destinations are 16-byte aligned at `first`).
+template <int T, int OPR, bool REQ, bool TREE, bool SHIFT, int MEM, bool GROUPED>
+__device__ __forceinline__ void fold_vectors(const Fold1& f, uint32_t first, uint32_t n, uint32_t lane) {
+    constexpr uint32_t S = DtInfo<T>::size, V = kVec<T>, kStep = kWaveSize * V;
+    uint32_t e = first;
+    if constexpr (!TREE) {
+        for (; e + kUnroll * kStep <= n; e += kUnroll * kStep)
+            fold_list<T, OPR, REQ, kUnroll, SHIFT, MEM, GROUPED>(f, (e + lane * V) * S);
+    }
+    for (; e + V <= n; e += kStep) {  // the lanes whose vector is whole
+        if (e + (lane + 1) * V <= n) {
+            if constexpr (TREE) fold_tree<T, REQ, SHIFT, MEM>(f, (e + lane * V) * S);
+            else fold_list<T, OPR, REQ, 1, SHIFT, MEM, GROUPED>(f, (e + lane * V) * S);
+        }
+    }
+    const uint32_t rest = (n - first) % V;
+    if (rest) fold_elems<T, OPR, REQ, TREE>(f, n - rest, rest, lane);
+}
+
+template <int T, int OPR, bool REQ, bool TREE, int MEM>
+__device__ __forceinline__ void fold_tile(const Fold1& f, uint32_t n, uint32_t flags, uint32_t lane) {
+    if (flags & UF_ALIGNED) {
+        if constexpr (!TREE && OPR == RO_SUM && T != DT_INT32) {
+            if (f.group) {
+                fold_vectors<T, OPR, REQ, TREE, false, MEM, true>(f, 0, n, lane);
+                return;
+            }
+        }
+        fold_vectors<T, OPR, REQ, TREE, false, MEM, false>(f, 0, n, lane);
+        return;
+    }
+    // Destinations that agree modulo 16: single elements up to their first 16-byte boundary, then
+    // vectors, the sources read at their element alignment. (A fold in groups goes by elements.)
+    if (!(flags & UF_DST_AGREE) || f.group) {
+        fold_elems<T, OPR, REQ, TREE>(f, 0, n, lane);
+        return;
+    }
+    uint32_t head = (uint32_t)(16u - ((uint64_t)f.dest(0) & 15u)) % 16u / DtInfo<T>::size;
+    if (head > n) head = n;
+    if (head) fold_elems<T, OPR, REQ, TREE>(f, 0, head, lane);
+    fold_vectors<T, OPR, REQ, TREE, true, MEM, false>(f, head, n, lane);
+}
+
+// Elements that tile 0 of a segment takes beyond its tile size, so that every other tile begins on a
+// 128-byte line of its (first) destination: a non-temporal store of part of a line costs a line.
+__device__ __forceinline__ uint32_t line_pad(uint64_t dst, uint32_t es, uint32_t flags) {
+    return flags & UF_ALIGNED ? 0u : (uint32_t)((128u - (dst & 127u)) & 127u) / es;
+}
+
+// Elements [e0, e0 + n) of a segment of `total` that its tile k covers; false if there are none.
+__device__ __forceinline__ bool tile_range(uint32_t k, uint32_t te, uint32_t pad, uint64_t total, uint64_t& e0, uint32_t& n) {
+    e0 = k ? (uint64_t)k * te + pad : 0;
+    if (e0 >= total) return false;
+    const uint64_t left = total - e0, most = k ? te : te + pad;
+    n = (uint32_t)(left < most ? left : most);
+    return true;
+}
+
+// Number of this wavefront in the launch (see hccl_executor for the XCD order).
+__device__ __forceinline__ uint32_t wave_number(bool xcd_order) {
+    uint32_t block = blockIdx.x;
+    if (xcd_order) {
+        const uint32_t B = gridDim.x, x = block % kXcds, j = block / kXcds;
+        block = x * (B / kXcds) + (x < B % kXcds ? x : B % kXcds) + j;
+    }
+    return uni(block * kWavesPerBlock + (threadIdx.x / kWaveSize));
+}
+
+template <int T, int MODE, bool TREE, int MEM>
+__global__ void __launch_bounds__(kBlockThreads) hccl_uniform_reduce(UniformArgs a, uint32_t redop) {
+    const uint32_t lane = __lane_id();
+    const ArgList args = (ArgList)__builtin_amdgcn_kernarg_segment_ptr();
+    Fold1 f;
+    f.nsrc = a.nsrc;
+    f.ndst = a.ndst;
+    f.group = a.group;
+    f.src = args + offsetof(UniformArgs, src) / 8;
+    for (uint32_t t = wave_number(a.flags & UF_XCD); t < a.ntiles; t += a.nworkers) {
+        const uint32_t g = a.nseg > 1 ? t / a.tiles_per_seg : 0u;
+        const uint32_t k = t - g * a.tiles_per_seg;
+        f.dst = args + offsetof(UniformArgs, dst) / 8 + (a.flags & UF_DST_PER_SEG ? g : 0u);
+        const uint32_t pad = line_pad(f.dst[0] + g * a.dst_step, DtInfo<T>::size, a.flags);
+        uint64_t e0;
+        uint32_t n;
+        if (!tile_range(k, a.tile_elems, pad, g + 1 < a.nseg ? a.seg_elems : a.last_elems, e0, n)) continue;
+        f.src_off = g * a.src_step + e0 * DtInfo<T>::size;
+        f.dst_off = g * a.dst_step + e0 * DtInfo<T>::size;
+        f.rot = a.flags & UF_ROTATE ? (g + 1 < a.nsrc ? g + 1 : 0u) : 0u;
+        f.flip = a.flags & UF_FLIP ? __brev(g) >> (__clz(a.nsrc) + 1) : 0u;
+        if constexpr (MODE == M_SUM) fold_tile<T, RO_SUM, false, TREE, MEM>(f, n, a.flags, lane);
+        else if constexpr (MODE == M_REQ) fold_tile<T, RO_SUM, true, TREE, MEM>(f, n, a.flags, lane);
+        else if (redop == RO_MAX) fold_tile<T, RO_MAX, false, TREE, MEM>(f, n, a.flags, lane);
+        else fold_tile<T, RO_MIN, false, TREE, MEM>(f, n, a.flags, lane);
+    }
+}
+
+// ------------------------------------------------------------------------------ copies
+// A wavefront copies one tile to `per_wave` of its destinations, all of the tile to one after the
+// other (the tile is read again for each, from the caches); its neighbours take the same tile to the
+// other destinations. Ordinary loads, non-temporal stores of whole lines.
+template <int ES, int U>
+__device__ __forceinline__ uint32_t copy_steps(const char* src, char* dst, uint32_t at, uint32_t nvec, uint32_t lane) {
+    for (; at + U * kWaveSize <= nvec; at += U * kWaveSize) {
+        u32x4 v[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) v[u] = vld_shifted<ES>(src + 16u * (at + u * kWaveSize + lane));
+#pragma unroll
+        for (int u = 0; u < U; ++u) vst_copy(dst + 16u * (at + u * kWaveSize + lane), v[u]);
+    }
+    return at;
+}
+
+// n elements from src to dst: 16-byte stores to dst's own alignment, after fewer than 16 bytes of
+// single elements, of 16-byte loads at whatever alignment that leaves the source.
+template <int ES>
+__device__ __forceinline__ void copy_run(const char* src, char* dst, uint32_t n, uint32_t lane) {
+    typedef typename std::conditional<ES == 2, uint16_t, uint32_t>::type W;
+    uint32_t head = (uint32_t)(16u - ((uint64_t)dst & 15u)) % 16u / ES;
+    if (head > n) head = n;
+    const uint32_t nvec = (n - head) * ES / 16u, rest = n - head - nvec * (16u / ES);
+    // the single elements before and after the vectors, one per lane
+    if (lane < head + rest) {
+        const uint32_t e = lane < head ? lane : n - rest + (lane - head);
+        *gp<W>(dst + (uint64_t)e * ES) = *gp<W>(src + (uint64_t)e * ES);
+    }
+    const char* s = src + head * ES;
+    char* d = dst + head * ES;
+    uint32_t at = copy_steps<ES, 8>(s, d, 0, nvec, lane);
+    at = copy_steps<ES, 4>(s, d, at, nvec, lane);
+    for (at += lane; at < nvec; at += kWaveSize) vst_copy(d + 16u * at, vld_shifted<ES>(s + 16u * at));
+}
+
+template <int ES>
+__global__ void __launch_bounds__(kBlockThreads) hccl_uniform_copy(UniformArgs a) {
+    const uint32_t lane = __lane_id();
+    const ArgList args = (ArgList)__builtin_amdgcn_kernarg_segment_ptr();
+    const ArgList srcs = args + offsetof(UniformArgs, src) / 8, dsts = args + offsetof(UniformArgs, dst) / 8;
+    const uint32_t sets = (a.ndst + a.per_wave - 1) / a.per_wave;
+    for (uint32_t t = wave_number(false); t < a.ntiles; t += a.nworkers) {
+        const uint32_t tile = sets > 1 ? t / sets : t, set = t - tile * sets;
+        const uint32_t g = a.nseg > 1 ? tile / a.tiles_per_seg : 0u;
+        const uint32_t pad = line_pad(dsts[a.flags & UF_DST_PER_SEG ? g : 0u] + g * a.dst_step, ES, a.flags);
+        uint64_t e0;
+        uint32_t n;
+        if (!tile_range(tile - g * a.tiles_per_seg, a.tile_elems, pad, g + 1 < a.nseg ? a.seg_elems : a.last_elems, e0, n)) continue;
+        const char* src = (const char*)(srcs[a.flags & UF_SRC_PER_SEG ? g : 0u] + g * a.src_step + e0 * ES);
+        const uint32_t j1 = (set + 1) * a.per_wave < a.ndst ? (set + 1) * a.per_wave : a.ndst;
+        for (uint32_t j = set * a.per_wave; j < j1; ++j) {
+            char* dst = (char*)(dsts[a.flags & UF_DST_PER_SEG ? g : j] + g * a.dst_step + e0 * ES);
+            if (dst != src) copy_run<ES>(src, dst, n, lane);
+        }
+    }
+}
+
+template <int T, int MODE, bool TREE>
+void launch_reduce(const UniformKernel& k, const UniformArgs& a, uint32_t blocks, hipStream_t s) {
+    if (k.mem & MEM_STORE) {
+        hipLaunchKernelGGL((hccl_uniform_reduce<T, MODE, TREE, MEM_STORE>), dim3(blocks), dim3(kBlockThreads), 0, s, a, k.redop);
+    } else if (k.mem & MEM_LOAD) {
+        hipLaunchKernelGGL((hccl_uniform_reduce<T, MODE, TREE, MEM_LOAD>), dim3(blocks), dim3(kBlockThreads), 0, s, a, k.redop);
+    } else {
+        hipLaunchKernelGGL((hccl_uniform_reduce<T, MODE, TREE, 0>), dim3(blocks), dim3(kBlockThreads), 0, s, a, k.redop);
+    }
+}
+
+// SUM of a floating type, in the folds and roundings there are
+template <int T>
+void launch_sum(const UniformKernel& k, const UniformArgs& a, uint32_t blocks, hipStream_t s) {
+    const bool tree = k.fold == FOLD_PAIRWISE;
+    if constexpr (T != DT_FP32) {
+        if (k.requant && tree) return launch_reduce<T, M_REQ, true>(k, a, blocks, s);
+        if (k.requant) return launch_reduce<T, M_REQ, false>(k, a, blocks, s);
+    }
+    if (tree) return launch_reduce<T, M_SUM, true>(k, a, blocks, s);
+    launch_reduce<T, M_SUM, false>(k, a, blocks, s);
+}
+
+template <int ES>
+void launch_copy(const UniformKernel& k, const UniformArgs& a, uint32_t blocks, hipStream_t s) {
+    hipLaunchKernelGGL((hccl_uniform_copy<ES>), dim3(blocks), dim3(kBlockThreads), 0, s, a);
+}
+
+}  // namespace
+
+hipError_t launch_uniform(const UniformKernel& k, const UniformArgs& a, uint32_t blocks, hipStream_t s) {
+    if (k.op == OP_COPY) {
+        if (dtype_size(k.dtype) == 2) launch_copy<2>(k, a, blocks, s);
+        else launch_copy<4>(k, a, blocks, s);
+    } else if (k.redop != RO_SUM) {
+        switch (k.dtype) {
+            case DT_BF16: launch_reduce<DT_BF16, M_MINMAX, false>(k, a, blocks, s); break;
+            case DT_FP16: launch_reduce<DT_FP16, M_MINMAX, false>(k, a, blocks, s); break;
+            case DT_FP32: launch_reduce<DT_FP32, M_MINMAX, false>(k, a, blocks, s); break;
+            default: launch_reduce<DT_INT32, M_MINMAX, false>(k, a, blocks, s); break;
+        }
+    } else {
+        switch (k.dtype) {
+            case DT_BF16: launch_sum<DT_BF16>(k, a, blocks, s); break;
+            case DT_FP16: launch_sum<DT_FP16>(k, a, blocks, s); break;
+            case DT_FP32: launch_sum<DT_FP32>(k, a, blocks, s); break;
+            default: launch_reduce<DT_INT32, M_SUM, false>(k, a, blocks, s); break;
+        }
+    }
+    return hipGetLastError();
+}
+
+}  // namespace hccl

@@ -298,26 +298,50 @@ struct ResidentArgs {
 
 enum TriggerCmp : uint32_t { CMP_EQ = 0, CMP_NE = 1, CMP_GE = 2, CMP_GT = 3, CMP_LE = 4, CMP_LT = 5 };
 
-// Kernel arguments of a one-step program launched inline: the step and its operands,
-// already resolved to addresses of element 0, travel in the launch packet.
-struct InlineArgs {
-    uint64_t nelem;
+// Kernel arguments of a uniform phase: its steps are one fold (or one copy) over up to kMaxOperands
+// segments of equal length, so the whole phase travels in the launch packet, every operand already
+// resolved to its address, and nothing is fetched from a program image first. Segment g reads
+// source i at src[i] + g * src_step (or the one source src[g]), and writes destination j at
+// dst[j] + g * dst_step (or the one destination dst[g]).
+enum UniformFlags : uint32_t {
+    UF_SRC_PER_SEG = 1,   // one source per segment: src[g]
+    UF_DST_PER_SEG = 2,   // one destination per segment: dst[g]
+    UF_ROTATE = 4,        // segment g folds sources g + 1, g + 2, ..., nsrc - 1, 0, ..., g
+    UF_FLIP = 64,         // source i of segment g is entry i with g, its bits reversed, flipped in
+    UF_ALIGNED = 8,       // every operand of every tile is 16-byte aligned
+    UF_DST_AGREE = 16,    // the destinations of one segment agree modulo 16
+    UF_XCD = 32,          // wavefronts numbered XCD by XCD
+};
+struct UniformArgs {
+    uint64_t seg_elems;   // elements of every segment but the last
+    uint64_t last_elems;  // elements of the last segment
+    uint64_t src_step;    // bytes from one segment to the next
+    uint64_t dst_step;
+    uint32_t nseg;
     uint32_t tile_elems;
-    uint32_t ntiles;
+    uint32_t tiles_per_seg;
+    uint32_t ntiles;      // of the launch; a copy has one set of tiles per `per_wave` destinations
     uint32_t nworkers;
-    uint32_t op;
-    uint32_t sig;
-    uint32_t redop;
-    uint32_t nsrc;
-    uint32_t ndst;
-    uint32_t group;
-    uint32_t es_first;   // element bytes of source 0 (and of a copy)
-    uint32_t es_rest;    // element bytes of the other sources
-    uint32_t es_out;     // element bytes of the destinations
-    uint32_t fold;       // Fold of the step
-    uint32_t requant;    // 1 = round every partial to the destination type
+    uint32_t nsrc;        // sources of one segment
+    uint32_t ndst;        // destinations of one segment
+    uint32_t group;       // fold order, as in Desc
+    uint32_t flags;       // UniformFlags
+    uint32_t per_wave;    // copies: destinations that one wavefront writes
     uint64_t src[kMaxOperands];
     uint64_t dst[kMaxOperands];
+};
+
+// Data accesses of a uniform phase that are ordinary ones; the others are non-temporal.
+enum MemFlags : uint8_t { MEM_LOAD = 1, MEM_STORE = 2 };
+
+// What selects the kernel of a uniform phase.
+struct UniformKernel {
+    uint8_t op;       // OP_COPY or OP_REDUCE
+    uint8_t dtype;
+    uint8_t redop;
+    uint8_t fold;     // Fold
+    bool requant;
+    uint8_t mem;      // MemFlags
 };
 
 }  // namespace hccl
