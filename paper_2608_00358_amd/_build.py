@@ -25,7 +25,7 @@ OBJDIR = os.path.join(PKG, "_build")
 ARCH = "gfx950"
 
 HOST_SOURCES = ["compiler.cpp", "validate.cpp"]
-EXECUTOR_SOURCES = ["executor_generic.hip", "executor_resident.hip", "executor.hip", "executor_uniform.hip"]
+EXECUTOR_SOURCES = ["executor_generic.hip", "executor_resident.hip", "executor.hip", "executor_uniform.hip", "executor_dynamic.hip"]
 HIP_SOURCES = EXECUTOR_SOURCES + ["api.cpp"]
 
 HIPCC_FLAGS = [

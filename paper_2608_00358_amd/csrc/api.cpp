@@ -29,6 +29,8 @@
 namespace hccl {
 hipError_t launch_executor(const LaunchArgs& a, uint32_t blocks, int kind, hipStream_t stream);
 hipError_t launch_uniform(const UniformKernel& k, const UniformArgs& a, uint32_t blocks, hipStream_t stream);
+uint32_t dynamic_waves_per_block(uint32_t P);
+hipError_t launch_dynamic(const DynamicArgs& a, uint32_t elem_bytes, uint32_t blocks, hipStream_t stream);
 hipError_t launch_fill_u32(uint32_t* p, uint64_t n, uint32_t v, hipStream_t stream);
 hipError_t launch_signal(uint64_t* word, uint64_t value, const ErrorRecord* err, hipStream_t stream);
 hipError_t executor_occupancy(int kind, int* blocks_per_cu);
@@ -556,6 +558,57 @@ hcclResult_t ensure_trace(hcclComm* c, uint64_t tiles) {
     return hcclSuccess;
 }
 
+// A lone AllToAllvDynamic (executor_dynamic.hip). Tiles of 4 KiB (2 / 4 / 8 / 16 KiB: 8 ranks x 256
+// tokens of 8 KiB 9.0 / 8.7 / 9.0 / 10.2 us; 16 ranks x 384 tokens of 2 KiB 15.8 / 11.5 / 13.8 / 16.6).
+// Up to 8 ranks one wavefront per tile that the capacities allow, as for the static exchange (8 ranks
+// x 2^18 rows of 256 bytes: 32 768 wavefronts in turn 181 us, one per tile 175). Above, where a
+// workgroup of 16 wavefronts plans, one workgroup per CU (64 ranks x 256 tokens of 4 KiB: one per CU
+// 30.8 us, two 33.7, four 39.5).
+constexpr uint64_t kDynamicTileBytes = 4096;
+
+// A program that is one AllToAllvDynamic, of the default tiles and of capacities whose row numbers
+// fit 32 bits, has kernels of its own (for above 8 ranks a workgroup plans with 16 wavefronts, so a
+// smaller configured bound keeps the executor's).
+bool lone_dynamic(const hcclComm* c, const std::vector<CollectiveSpec>& specs) {
+    if (specs.size() != 1 || specs[0].coll != COLL_ALLTOALLV_DYNAMIC || specs[0].tile_bytes != 0) return false;
+    const CollectiveSpec& s = specs[0];
+    const uint64_t cap = std::max(s.send_cap, s.recv_cap), P = (uint64_t)s.P;
+    if (cap >= (1ull << 31) / P || cap * s.row_elems * dtype_size((uint32_t)s.dtype) / kDynamicTileBytes + P >= (1ull << 31) / P) return false;
+    // a kernel that waits for something still to come may leave a CU room for four wavefronts and
+    // not for sixteen, and what it waits for may be this call
+    if (s.P > 8 && (trigger_pending(c->device) || resident_running(c->device))) return false;
+    return c->cfg.max_workers <= 0 || (uint32_t)c->cfg.max_workers >= dynamic_waves_per_block((uint32_t)s.P);
+}
+
+hipError_t launch_lone_dynamic(const hcclComm* c, const Call& k, hipStream_t s, uint32_t& workers) {
+    DynamicArgs a;
+    const uint32_t P = (uint32_t)k.spec.P, es = dtype_size((uint32_t)k.spec.dtype);
+    a.counts = (const int64_t*)k.meta[META_COUNTS];
+    a.sdispls = (const int64_t*)k.meta[META_SDISPLS];
+    a.rdispls = (const int64_t*)k.meta[META_RDISPLS];
+    a.recvcounts = (int64_t*)k.meta[META_RECVCOUNTS];
+    a.error = c->d_error;
+    a.row_elems = k.spec.row_elems;
+    a.send_cap = (uint32_t)k.spec.send_cap;
+    a.recv_cap = (uint32_t)k.spec.recv_cap;
+    a.P = P;
+    const uint64_t tb = kDynamicTileBytes;
+    a.tile_shift = (uint32_t)__builtin_ctzll(tb / es);
+    for (uint32_t i = 0; i < P; ++i) {
+        a.send[i] = (uint64_t)(uintptr_t)k.send[i];
+        a.recv[i] = (uint64_t)(uintptr_t)k.recv[i];
+    }
+    // tiles of any layout that fits: a source's pairs hold at most its capacity, and each pair ends
+    // in at most one partial tile
+    const uint64_t te = tb / es, wpb = dynamic_waves_per_block(P);
+    const uint64_t tiles = P * ((k.spec.send_cap * k.spec.row_elems + te - 1) / te + P);
+    uint64_t most = P <= 8 ? kMaxGridWorkers : (uint64_t)c->cus * wpb;
+    if (c->cfg.max_workers > 0) most = std::min<uint64_t>(most, (uint64_t)c->cfg.max_workers / wpb * wpb);
+    const uint32_t blocks = (uint32_t)((std::min(tiles, most) + wpb - 1) / wpb);
+    a.nworkers = workers = blocks * (uint32_t)wpb;
+    return launch_dynamic(a, es, blocks, s);
+}
+
 // Launches one uniform phase on the buffers `bufs`; the wavefronts of the launch go to `workers`.
 // One wavefront per tile, as for every launch in which no tile waits (see launch_shape).
 hipError_t launch_uniform_phase(const hcclComm* c, const UniformPhase& u, char* const* bufs, hipStream_t s, uint32_t& workers) {
@@ -730,7 +783,8 @@ hcclResult_t run_packet(hcclComm* c, const std::vector<Call>& calls) {
     int kind = 0;
     info.tickets = a.dynamic;
     const bool packed = inline_eligible(c, triggered);
-    info.inline_launch = packed && all_uniform(dp->prog) ? 1 : 0;
+    const bool lone = packed && lone_dynamic(c, specs);
+    info.inline_launch = lone || (packed && all_uniform(dp->prog)) ? 1 : 0;
 
     // a program's counters serve one launch at a time, and the communicator's scratch one
     // program at a time: order such launches across streams. A captured launch is left out of
@@ -756,7 +810,11 @@ hcclResult_t run_packet(hcclComm* c, const std::vector<Call>& calls) {
     hipError_t e = hipSuccess;
     for (uint32_t q = 0; q < nph; ++q) {
         if (q > 0) a.wait_addr = nullptr;  // later phases follow the first on the stream: only it waits for a trigger
-        if (packed && dp->prog.uniform[q].ok) {
+        if (lone) {
+            e = launch_lone_dynamic(c, calls[0], s, a.nworkers);
+            if (e != hipSuccess) return hip_fail(e, "dynamic launch");
+            hlog(c, 3, "launched from the launch packet: %u wavefronts", a.nworkers);
+        } else if (packed && dp->prog.uniform[q].ok) {
             e = launch_uniform_phase(c, dp->prog.uniform[q], a.bufs, s, a.nworkers);
             if (e != hipSuccess) return hip_fail(e, "uniform launch");
             hlog(c, 3, "launched phase %u of %u from the launch packet: %u wavefronts", q + 1, nph, a.nworkers);

@@ -5,7 +5,7 @@
 // table, descriptor, operands, buffer table, each a dependent read of memory. Here tile number and
 // kernel arguments give every address by arithmetic, the pointers in scalar registers. Every kernel
 // is compiled for one type, one operator and one fold, with as many loads in flight as that allows.
-#include "executor_device.h"
+#include "executor_runs.h"
 
 namespace hccl {
 
@@ -294,21 +294,6 @@ __device__ __forceinline__ void fold_tile(const Fold1& f, uint32_t n, uint32_t f
     fold_vectors<T, OPR, REQ, TREE, true, MEM, false>(f, head, n, lane);
 }
 
-// Elements that tile 0 of a segment takes beyond its tile size, so that every other tile begins on a
-// 128-byte line of its (first) destination: a non-temporal store of part of a line costs a line.
-__device__ __forceinline__ uint32_t line_pad(uint64_t dst, uint32_t es, uint32_t flags) {
-    return flags & UF_ALIGNED ? 0u : (uint32_t)((128u - (dst & 127u)) & 127u) / es;
-}
-
-// Elements [e0, e0 + n) of a segment of `total` that its tile k covers; false if there are none.
-__device__ __forceinline__ bool tile_range(uint32_t k, uint32_t te, uint32_t pad, uint64_t total, uint64_t& e0, uint32_t& n) {
-    e0 = k ? (uint64_t)k * te + pad : 0;
-    if (e0 >= total) return false;
-    const uint64_t left = total - e0, most = k ? te : te + pad;
-    n = (uint32_t)(left < most ? left : most);
-    return true;
-}
-
 // Number of this wavefront in the launch (see hccl_executor for the XCD order).
 __device__ __forceinline__ uint32_t wave_number(bool xcd_order) {
     uint32_t block = blockIdx.x;
@@ -332,7 +317,7 @@ __global__ void __launch_bounds__(kBlockThreads) hccl_uniform_reduce(UniformArgs
         const uint32_t g = a.nseg > 1 ? t / a.tiles_per_seg : 0u;
         const uint32_t k = t - g * a.tiles_per_seg;
         f.dst = args + offsetof(UniformArgs, dst) / 8 + (a.flags & UF_DST_PER_SEG ? g : 0u);
-        const uint32_t pad = line_pad(f.dst[0] + g * a.dst_step, DtInfo<T>::size, a.flags);
+        const uint32_t pad = a.flags & UF_ALIGNED ? 0u : line_pad(f.dst[0] + g * a.dst_step, DtInfo<T>::size);
         uint64_t e0;
         uint32_t n;
         if (!tile_range(k, a.tile_elems, pad, g + 1 < a.nseg ? a.seg_elems : a.last_elems, e0, n)) continue;
@@ -351,38 +336,6 @@ __global__ void __launch_bounds__(kBlockThreads) hccl_uniform_reduce(UniformArgs
 // A wavefront copies one tile to `per_wave` of its destinations, all of the tile to one after the
 // other (the tile is read again for each, from the caches); its neighbours take the same tile to the
 // other destinations. Ordinary loads, non-temporal stores of whole lines.
-template <int ES, int U>
-__device__ __forceinline__ uint32_t copy_steps(const char* src, char* dst, uint32_t at, uint32_t nvec, uint32_t lane) {
-    for (; at + U * kWaveSize <= nvec; at += U * kWaveSize) {
-        u32x4 v[U];
-#pragma unroll
-        for (int u = 0; u < U; ++u) v[u] = vld_shifted<ES>(src + 16u * (at + u * kWaveSize + lane));
-#pragma unroll
-        for (int u = 0; u < U; ++u) vst_copy(dst + 16u * (at + u * kWaveSize + lane), v[u]);
-    }
-    return at;
-}
-
-// n elements from src to dst: 16-byte stores to dst's own alignment, after fewer than 16 bytes of
-// single elements, of 16-byte loads at whatever alignment that leaves the source.
-template <int ES>
-__device__ __forceinline__ void copy_run(const char* src, char* dst, uint32_t n, uint32_t lane) {
-    typedef typename std::conditional<ES == 2, uint16_t, uint32_t>::type W;
-    uint32_t head = (uint32_t)(16u - ((uint64_t)dst & 15u)) % 16u / ES;
-    if (head > n) head = n;
-    const uint32_t nvec = (n - head) * ES / 16u, rest = n - head - nvec * (16u / ES);
-    // the single elements before and after the vectors, one per lane
-    if (lane < head + rest) {
-        const uint32_t e = lane < head ? lane : n - rest + (lane - head);
-        *gp<W>(dst + (uint64_t)e * ES) = *gp<W>(src + (uint64_t)e * ES);
-    }
-    const char* s = src + head * ES;
-    char* d = dst + head * ES;
-    uint32_t at = copy_steps<ES, 8>(s, d, 0, nvec, lane);
-    at = copy_steps<ES, 4>(s, d, at, nvec, lane);
-    for (at += lane; at < nvec; at += kWaveSize) vst_copy(d + 16u * at, vld_shifted<ES>(s + 16u * at));
-}
-
 template <int ES>
 __global__ void __launch_bounds__(kBlockThreads) hccl_uniform_copy(UniformArgs a) {
     const uint32_t lane = __lane_id();
@@ -392,7 +345,7 @@ __global__ void __launch_bounds__(kBlockThreads) hccl_uniform_copy(UniformArgs a
     for (uint32_t t = wave_number(false); t < a.ntiles; t += a.nworkers) {
         const uint32_t tile = sets > 1 ? t / sets : t, set = t - tile * sets;
         const uint32_t g = a.nseg > 1 ? tile / a.tiles_per_seg : 0u;
-        const uint32_t pad = line_pad(dsts[a.flags & UF_DST_PER_SEG ? g : 0u] + g * a.dst_step, ES, a.flags);
+        const uint32_t pad = a.flags & UF_ALIGNED ? 0u : line_pad(dsts[a.flags & UF_DST_PER_SEG ? g : 0u] + g * a.dst_step, ES);
         uint64_t e0;
         uint32_t n;
         if (!tile_range(tile - g * a.tiles_per_seg, a.tile_elems, pad, g + 1 < a.nseg ? a.seg_elems : a.last_elems, e0, n)) continue;

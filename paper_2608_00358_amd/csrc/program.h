@@ -331,6 +331,25 @@ struct UniformArgs {
     uint64_t dst[kMaxOperands];
 };
 
+// Kernel arguments of a lone AllToAllvDynamic (DynA2A, its buffers resolved to addresses). Row numbers
+// fit 32 bits: P times the larger capacity is below 2^31.
+struct DynamicArgs {
+    const int64_t* counts;     // as in DynA2A; the optional arrays are NULL where the call has none
+    const int64_t* sdispls;
+    const int64_t* rdispls;
+    int64_t* recvcounts;
+    ErrorRecord* error;
+    uint64_t row_elems;
+    uint32_t send_cap;         // rows
+    uint32_t recv_cap;
+    uint32_t P;
+    uint32_t tile_shift;       // elements per tile, as a power of two
+    uint32_t nworkers;
+    uint32_t pad;
+    uint64_t send[kMaxRanks];
+    uint64_t recv[kMaxRanks];
+};
+
 // Data accesses of a uniform phase that are ordinary ones; the others are non-temporal.
 enum MemFlags : uint8_t { MEM_LOAD = 1, MEM_STORE = 2 };
 

@@ -1,0 +1,155 @@
+"""GPU parity of the calls that travel in their launch packets (uniform phases and a lone
+AllToAllvDynamic), at the edges of their tiles, against the oracle: bit for bit, guard bands included.
+With the default tile size a fused call takes these kernels; a configured one takes the executor's."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+import paper_2608_00358_amd as H
+from gpu_helpers import Guarded, first_mismatch, same_bits, to_device
+from test_gpu_dynamic import random_counts, run_dynamic
+from test_gpu_orders import run_ar, run_rs
+from test_gpu_parity import run_allgather, run_allreduce, run_reduce_scatter
+
+pytestmark = pytest.mark.gpu
+
+# one element, less than a vector, around a wavefront's vectors, around two, several tiles
+SIZES = [1, 5, 511, 513, 1029, 9001]
+
+
+@pytest.mark.parametrize("dt", ["bf16", "fp16", "fp32", "int32"])
+@pytest.mark.parametrize("P", [2, 3, 8, 9, 17, 64])
+def test_sum_in_list_order(dt, P):
+    for n in SIZES:
+        assert run_allreduce(P, n, dt)["inline_launch"] == 1
+    run_reduce_scatter(P, 517, dt)
+
+
+@pytest.mark.parametrize("dt", ["bf16", "fp16", "fp32", "int32"])
+@pytest.mark.parametrize("op", ["max", "min"])
+@pytest.mark.parametrize("P", [2, 9, 16])
+def test_max_min(dt, op, P):
+    for n in SIZES:
+        assert run_allreduce(P, n, dt, op=op)["inline_launch"] == 1
+    run_reduce_scatter(P, 517, dt, op=op, order="ring")
+
+
+@pytest.mark.parametrize("dt", ["bf16", "fp16", "fp32", "int32"])
+@pytest.mark.parametrize("requant", [False, True])
+@pytest.mark.parametrize("order,P", [("ring", 3), ("ring", 16), ("halving", 2), ("halving", 4), ("halving", 8),
+                                     ("halving", 16), ("halving", 32), ("halving", 64), ("ascending", 8)])
+def test_orders_and_requantised_partials(dt, requant, order, P):
+    for n in SIZES:
+        assert run_ar(P, n, dt, order, requant)["inline_launch"] == 1
+    run_rs(P, 517, dt, order, requant)
+
+
+@pytest.mark.parametrize("dt", ["bf16", "fp32"])
+@pytest.mark.parametrize("P,group", [(16, 8), (64, 8), (6, 3)])
+@pytest.mark.parametrize("phases", ["auto", "levels"])
+def test_two_level_in_one_and_two_phases(dt, P, group, phases):
+    for n in (9001, 64 * P * 3):  # unequal sub-shards (the executor's kernels), then equal ones
+        info = run_allreduce(P, n, dt, algo="two_level", group_size=group, phases=phases)
+        assert info["num_phases"] == (2 if phases == "levels" and P >= 16 else 1)
+    assert info["inline_launch"] == 1
+
+
+@pytest.mark.parametrize("dt", ["bf16", "int32"])
+@pytest.mark.parametrize("P", [1, 2, 5, 8, 33, 64])
+def test_allgather(dt, P):
+    for m in (1, 7, 2047, 2049, 5001):
+        run_allgather(P, m, dt)
+
+
+@pytest.mark.parametrize("dt,order", [("bf16", "halving"), ("fp16", "ring"), ("fp32", "halving")])
+@pytest.mark.parametrize("op", ["sum", "max"])
+def test_every_offset_from_a_boundary(dt, order, op):
+    """Views that start 1, 2, ... elements into their allocation; sources and results agree or not."""
+    P, n = 8, 2100
+    rng = np.random.default_rng(3)
+    x = rng.standard_normal((P, n)).astype(np.float32)
+    bits = np.stack([to_device_bits(v, dt) for v in x])
+    want = oracle.allreduce_ordered(bits, dt, order=order, shard=-(-(-(-n // P)) // 64) * 64) if op == "sum" else \
+        oracle.allreduce(bits, dt, op=op)
+    with H.Comm(P, device=0, order=order) as c:
+        for a, b in ((1, 1), (3, 3), (0, 1), (5, 2), (7, 0)):
+            print(f"offsets {a} {b} {dt} {op}", flush=True)
+            send = [to_device(np.concatenate([np.zeros(a, bits.dtype), bits[r]]), dt)[a:] for r in range(P)]
+            outs = [Guarded(n + b, dt) for _ in range(P)]
+            H.hccl_allreduce(c.handle, send, [o.view[b:] for o in outs], n, dt, op)
+            torch.cuda.synchronize()
+            for r in range(P):
+                got = outs[r].result()[b:]
+                assert same_bits(got, want[r], dt), f"rank {r}: {first_mismatch(got, want[r])}"
+                assert outs[r].guards_intact()
+
+
+def to_device_bits(v, dt):
+    t = torch.from_numpy(v)
+    if dt == "fp32":
+        return v
+    return t.to({"bf16": torch.bfloat16, "fp16": torch.float16}[dt]).view(torch.int16).numpy().view(np.uint16)
+
+
+@pytest.mark.parametrize("op,order,requant", [("sum", "ascending", False), ("sum", "halving", True), ("max", "ring", False)])
+@pytest.mark.parametrize("dt", ["bf16", "fp16"])
+def test_every_kind_of_value(op, order, requant, dt):
+    """Random bit patterns: infinities, NaNs, subnormal and largest numbers."""
+    P, n = 4, 20000
+    x = np.random.default_rng(5).integers(0, 1 << 16, (P, n)).astype(np.uint16)
+    with H.Comm(P, device=0, order=order, requantize=int(requant)) as c:
+        send = [to_device(x[r], dt) for r in range(P)]
+        outs = [Guarded(n, dt) for _ in range(P)]
+        H.hccl_allreduce(c.handle, send, [o.view for o in outs], n, dt, op)
+        torch.cuda.synchronize()
+    want = oracle.allreduce(x, dt, op=op) if op == "max" else \
+        oracle.allreduce_ordered(x, dt, order=order, shard=-(-(-(-n // P)) // 64) * 64, requant=requant)
+    for r in range(P):
+        assert same_bits(outs[r].result(), want[r], dt), first_mismatch(outs[r].result(), want[r])
+
+
+# ------------------------------------------------------------------ AllToAllvDynamic
+@pytest.mark.parametrize("P", [7, 8, 9, 16, 17, 33, 64])
+@pytest.mark.parametrize("R,dt", [(1, "bf16"), (5, "int32"), (2048, "bf16"), (3001, "fp32")])
+def test_dynamic_layouts(P, R, dt):
+    rows = 9 if R < 100 else 3
+    counts = random_counts(P, rows, seed=P + R, zero_frac=0.4)
+    ok, info = run_dynamic(P, R, dt, counts, int(counts.sum(axis=1).max()) + 1, int(counts.sum(axis=0).max()), seed=P)
+    assert ok and info["inline_launch"] == 1
+    # explicit offsets, the received ranges in another order with gaps
+    rng = np.random.default_rng(P)
+    sd, rd, cap = np.cumsum(counts, axis=1) - counts, np.zeros((P, P), np.int64), 0
+    for d in range(P):
+        at = 0
+        for s in rng.permutation(P):
+            rd[d, s] = at
+            at += counts[s, d] + int(rng.integers(0, 2))
+        cap = max(cap, at)
+    assert run_dynamic(P, R, dt, counts, int(counts.sum(axis=1).max()), cap, sd=sd, rd=rd, seed=P)[0]
+
+
+@pytest.mark.parametrize("P", [8, 20, 64])
+@pytest.mark.parametrize("case", ["send_over", "recv_over", "negative", "huge", "overlap", "offset_out", "recv_offset_out"])
+def test_dynamic_rejects_as_a_workgroup(P, case):
+    R = 6
+    counts = random_counts(P, 5, seed=P, zero_frac=0.0) + 1
+    send_cap, recv_cap = int(counts.sum(axis=1).max()), int(counts.sum(axis=0).max())
+    sd = rd = None
+    s, d = P - 1, P // 2
+    if case == "send_over":
+        send_cap -= 1
+    elif case == "recv_over":
+        recv_cap -= 1
+    elif case == "negative":
+        counts[s, d] = -1
+    elif case == "huge":
+        counts[s, d] = (1 << 32) + 1
+    elif case in ("overlap", "recv_offset_out"):
+        back = counts.T
+        rd = np.cumsum(back, axis=1) - back
+        rd[d, s] = rd[d, s] - 1 if case == "overlap" else recv_cap - counts[s, d] + 1
+    elif case == "offset_out":
+        sd = np.cumsum(counts, axis=1) - counts
+        sd[s, d] = send_cap - counts[s, d] + 1
+    assert not run_dynamic(P, R, "bf16", counts, send_cap, recv_cap, sd=sd, rd=rd, seed=1)[0]
