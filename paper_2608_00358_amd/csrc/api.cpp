@@ -627,15 +627,11 @@ hipError_t launch_uniform_phase(const hcclComm* c, const UniformPhase& u, char* 
     a.flags = u.flags;
     a.per_wave = u.per_wave;
     // tiles are whole vectors, so the first element of every segment decides the alignment
-    uint64_t any = 0, differ = 0;
+    uint64_t any = 0;
     for (size_t i = 0; i < u.srcs.size(); ++i) any |= a.src[i] = (uint64_t)(uintptr_t)bufs[u.srcs[i].buf] + u.srcs[i].offset;
-    for (size_t i = 0; i < u.dsts.size(); ++i) {
-        any |= a.dst[i] = (uint64_t)(uintptr_t)bufs[u.dsts[i].buf] + u.dsts[i].offset;
-        differ |= a.dst[i] ^ a.dst[0];
-    }
+    for (size_t i = 0; i < u.dsts.size(); ++i) any |= a.dst[i] = (uint64_t)(uintptr_t)bufs[u.dsts[i].buf] + u.dsts[i].offset;
     if (u.nseg > 1) any |= u.src_step | u.dst_step;
     if (any % 16 == 0) a.flags |= UF_ALIGNED;
-    if (differ % 16 == 0 || a.ndst == 1) a.flags |= UF_DST_AGREE;
     const uint32_t wpb = (uint32_t)executor_waves_per_block();
     workers = std::min<uint32_t>(a.ntiles, kMaxGridWorkers);
     if (c->cfg.max_workers > 0) workers = std::min<uint32_t>(workers, (uint32_t)c->cfg.max_workers);

@@ -11,8 +11,6 @@ namespace hccl {
 
 namespace {
 
-typedef const __attribute__((address_space(4))) uint64_t* ArgList;
-
 // Inclusive prefix sum over the lanes of a wavefront.
 __device__ __forceinline__ uint32_t scan32(uint32_t v, uint32_t lane) {
 #pragma unroll
@@ -60,8 +58,7 @@ template <int ES>
 __global__ void __launch_bounds__(kBlockThreads) hccl_dynamic_small(DynamicArgs a) {
     const uint32_t lane = __lane_id();
     const uint32_t wave = uni(blockIdx.x * kWavesPerBlock + threadIdx.x / kWaveSize);
-    const ArgList args = (ArgList)__builtin_amdgcn_kernarg_segment_ptr();
-    const ArgList send = args + offsetof(DynamicArgs, send) / 8, recv = args + offsetof(DynamicArgs, recv) / 8;
+    const uint64_t send = lane_entry(offsetof(DynamicArgs, send), lane), recv = lane_entry(offsetof(DynamicArgs, recv), lane);
     const uint32_t P = a.P, PP = P * P;
     const bool on = lane < PP;
     const uint32_t d = on ? lane / P : 0u, s = on ? lane - d * P : 0u;
@@ -108,7 +105,7 @@ __global__ void __launch_bounds__(kBlockThreads) hccl_dynamic_small(DynamicArgs 
     for (uint32_t j = wave; j < J; j += a.nworkers) {
         const uint32_t p = (uint32_t)__popcll(__ballot(incl <= j));
         const uint32_t pd = p / P, ps = p - pd * P;
-        copy_pair_tile<ES>(a, (const char*)send[ps], (char*)recv[pd], lane32(so, p), lane32(ro, p), lane32(c, p),
+        copy_pair_tile<ES>(a, (const char*)from_lane(send, ps), (char*)from_lane(recv, pd), lane32(so, p), lane32(ro, p), lane32(c, p),
                            j - (p ? lane32(incl, p - 1) : 0u), lane);
     }
 }
@@ -129,8 +126,7 @@ __global__ void __launch_bounds__(kPlanWaves * kWaveSize) hccl_dynamic_wide(Dyna
     __shared__ uint32_t l_row[kMaxRanks];                  // tiles of a row
     __shared__ uint32_t l_bad;
     const uint32_t lane = __lane_id(), w = uni(threadIdx.x / kWaveSize);
-    const ArgList args = (ArgList)__builtin_amdgcn_kernarg_segment_ptr();
-    const ArgList send = args + offsetof(DynamicArgs, send) / 8, recv = args + offsetof(DynamicArgs, recv) / 8;
+    const uint64_t send = lane_entry(offsetof(DynamicArgs, send), lane), recv = lane_entry(offsetof(DynamicArgs, recv), lane);
     const uint32_t P = a.P, rows = (P + kPlanWaves - 1) / kPlanWaves;
     const uint32_t most = a.send_cap < a.recv_cap ? a.send_cap : a.recv_cap;
     if (threadIdx.x == 0) l_bad = 0;
@@ -208,7 +204,7 @@ __global__ void __launch_bounds__(kPlanWaves * kWaveSize) hccl_dynamic_wide(Dyna
         const uint32_t mine = lane < P ? l_tiles[s * kPlanStride + lane] : ~0u;
         const uint32_t d = (uint32_t)__popcll(__ballot(mine <= jr));
         const uint32_t at = s * kPlanStride + d;
-        copy_pair_tile<ES>(a, (const char*)send[s], (char*)recv[d], uni(l_send[at]), uni(l_recv[at]), uni(l_count[at]),
+        copy_pair_tile<ES>(a, (const char*)from_lane(send, s), (char*)from_lane(recv, d), uni(l_send[at]), uni(l_recv[at]), uni(l_count[at]),
                            jr - (d ? lane32(mine, d - 1) : 0u), lane);
     }
 }

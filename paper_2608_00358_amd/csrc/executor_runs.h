@@ -6,6 +6,11 @@
 namespace hccl {
 namespace {
 
+// Entry `lane` of the 64-entry list at byte `off` of the kernel arguments.
+__device__ __forceinline__ uint64_t lane_entry(size_t off, uint32_t lane) {
+    return ((const uint64_t*)((const char*)__builtin_amdgcn_kernarg_segment_ptr() + off))[lane];
+}
+
 // Elements that tile 0 of a segment takes beyond its tile size, so that every other tile begins on a
 // 128-byte line of its (first) destination: a non-temporal store of part of a line costs a line.
 __device__ __forceinline__ uint32_t line_pad(uint64_t dst, uint32_t es) {

@@ -3,7 +3,7 @@
 //
 // A wavefront of the descriptor executor finds its tile through the program image: header, tile
 // table, descriptor, operands, buffer table, each a dependent read of memory. Here tile number and
-// kernel arguments give every address by arithmetic, the pointers in scalar registers. Every kernel
+// kernel arguments give every address by arithmetic. Every kernel
 // is compiled for one type, one operator and one fold, with as many loads in flight as that allows.
 #include "executor_runs.h"
 
@@ -15,9 +15,6 @@ enum Mode { M_SUM, M_MINMAX, M_REQ };  // M_REQ: SUM, every partial rounded to t
 
 constexpr int kBatch = 8;   // sources whose loads are in flight together
 constexpr int kUnroll = 2;  // 16-byte vectors per lane and source in flight
-
-// The operand lists in the kernel-argument segment: uniform indexes make scalar loads.
-typedef const __attribute__((address_space(4))) uint64_t* ArgList;
 
 template <int T> constexpr int kVec = 16 / DtInfo<T>::size;  // elements of a 16-byte vector
 
@@ -70,18 +67,21 @@ __device__ __forceinline__ void combine(A (&a)[kVec<T>], const A (&x)[kVec<T>]) 
     if constexpr (REQ) widen<T, A>(narrow<T, A>(a), a);
 }
 
-// The fold of one tile's segment: where its sources and destinations are.
+// The fold of one tile's segment: where its sources and destinations are. Lane j holds entry j of
+// the operand lists: one vector load brings a list of 64, where scalar loads of the entries in
+// turn would wait for eight cache lines one after the other.
 struct Fold1 {
-    ArgList src, dst;
+    uint64_t src, dst;
     uint64_t src_off, dst_off;  // bytes from a list entry to element 0 of the tile
     uint32_t nsrc, ndst, group;
     uint32_t rot, flip;         // source i of the fold is entry (i + rot) mod nsrc, or i ^ flip
+    uint32_t first;             // entry of destination 0
     __device__ __forceinline__ const char* source(uint32_t i) const {
         uint32_t k = i + rot;
         if (k >= nsrc) k -= nsrc;
-        return (const char*)(src[k ^ flip] + src_off);
+        return (const char*)(from_lane(src, k ^ flip) + src_off);
     }
-    __device__ __forceinline__ char* dest(uint32_t j) const { return (char*)(dst[j] + dst_off); }
+    __device__ __forceinline__ char* dest(uint32_t j) const { return (char*)(from_lane(dst, first + j) + dst_off); }
 };
 
 // MEM: which accesses are ordinary (MemFlags); the others are non-temporal. SHIFT: addresses aligned only to the element.
@@ -91,10 +91,12 @@ __device__ __forceinline__ u32x4 load_vec(const char* p) {
     else if constexpr (MEM & MEM_LOAD) return *gp<u32x4>(p);
     else return __builtin_nontemporal_load(gp<u32x4>(p));
 }
-template <int MEM>
+template <int T, bool SHIFT, int MEM>
 __device__ __forceinline__ void store_vec(char* p, u32x4 v) {
-    if constexpr (MEM & MEM_STORE) *gp<u32x4>(p) = v;
-    else __builtin_nontemporal_store(v, gp<u32x4>(p));
+    typedef typename std::conditional<DtInfo<T>::size == 2, u32x4_a2, u32x4_a4>::type VU;
+    typedef typename std::conditional<SHIFT, VU, u32x4>::type V;
+    if constexpr (MEM & MEM_STORE) *gp<V>(p) = (V)v;
+    else __builtin_nontemporal_store((V)v, gp<V>(p));
 }
 
 // Fold in list order of U vectors per lane, the first at byte `at` of the tile, 1 KiB apart.
@@ -152,7 +154,7 @@ __device__ __forceinline__ void fold_list(const Fold1& f, uint32_t at) {
     for (uint32_t d = 0; d < f.ndst; ++d) {
         char* b = f.dest(d);
 #pragma unroll
-        for (int u = 0; u < U; ++u) store_vec<MEM>(b + (at + u * 1024u), w[u]);
+        for (int u = 0; u < U; ++u) store_vec<T, SHIFT, MEM>(b + (at + u * 1024u), w[u]);
     }
 }
 
@@ -203,11 +205,11 @@ __device__ __forceinline__ void fold_tree(const Fold1& f, uint32_t at) {
         }
     }
     const u32x4 w = narrow<T, A>(v);
-    for (uint32_t d = 0; d < f.ndst; ++d) store_vec<MEM>(f.dest(d) + at, w);
+    for (uint32_t d = 0; d < f.ndst; ++d) store_vec<T, SHIFT, MEM>(f.dest(d) + at, w);
 }
 
-// Elements [first, first + count) of the tile, one per lane (heads and tails of misaligned tiles,
-// tiles whose destinations disagree modulo 16). The tree's stack has six levels here.
+// Elements [first, first + count) of the tile, one per lane: what is left after whole wavefront steps
+// if it is less than a vector. The tree's stack has six levels here.
 template <int T, int OPR, bool REQ, bool TREE>
 __device__ __forceinline__ void fold_elems(const Fold1& f, uint32_t first, uint32_t count, uint32_t lane) {
     typedef typename DtInfo<T>::acc A;
@@ -251,47 +253,44 @@ __device__ __forceinline__ void fold_elems(const Fold1& f, uint32_t first, uint3
     }
 }
 
-// Elements [first, n) of the tile in vectors (its destinations are 16-byte aligned at `first`).
+// The n elements of a tile. The last step takes what is left over whole wavefront steps: the lanes
+// whose vector is whole, and one lane more that takes the last vector's worth of elements, some of
+// them a second time (in the same step, so that in place every source is read before any result
+// is stored). SHIFT: addresses aligned only to the element.
 template <int T, int OPR, bool REQ, bool TREE, bool SHIFT, int MEM, bool GROUPED>
-__device__ __forceinline__ void fold_vectors(const Fold1& f, uint32_t first, uint32_t n, uint32_t lane) {
+__device__ __forceinline__ void fold_vectors(const Fold1& f, uint32_t n, uint32_t lane) {
     constexpr uint32_t S = DtInfo<T>::size, V = kVec<T>, kStep = kWaveSize * V;
-    uint32_t e = first;
+    uint32_t e = 0;
     if constexpr (!TREE) {
         for (; e + kUnroll * kStep <= n; e += kUnroll * kStep)
             fold_list<T, OPR, REQ, kUnroll, SHIFT, MEM, GROUPED>(f, (e + lane * V) * S);
     }
-    for (; e + V <= n; e += kStep) {  // the lanes whose vector is whole
-        if (e + (lane + 1) * V <= n) {
-            if constexpr (TREE) fold_tree<T, REQ, SHIFT, MEM>(f, (e + lane * V) * S);
-            else fold_list<T, OPR, REQ, 1, SHIFT, MEM, GROUPED>(f, (e + lane * V) * S);
-        }
+    for (; e + kStep <= n; e += kStep) {
+        if constexpr (TREE) fold_tree<T, REQ, SHIFT, MEM>(f, (e + lane * V) * S);
+        else fold_list<T, OPR, REQ, 1, SHIFT, MEM, GROUPED>(f, (e + lane * V) * S);
     }
-    const uint32_t rest = (n - first) % V;
-    if (rest) fold_elems<T, OPR, REQ, TREE>(f, n - rest, rest, lane);
+    if (e == n) return;
+    const uint32_t whole = (n - e) / V;
+    if (whole == 0) {
+        fold_elems<T, OPR, REQ, TREE>(f, e, n - e, lane);
+    } else if (lane * V < n - e) {
+        const uint32_t at = (lane < whole ? e + lane * V : n - V) * S;
+        if constexpr (TREE) fold_tree<T, REQ, true, MEM>(f, at);
+        else fold_list<T, OPR, REQ, 1, true, MEM, GROUPED>(f, at);
+    }
 }
 
 template <int T, int OPR, bool REQ, bool TREE, int MEM>
-__device__ __forceinline__ void fold_tile(const Fold1& f, uint32_t n, uint32_t flags, uint32_t lane) {
-    if (flags & UF_ALIGNED) {
-        if constexpr (!TREE && OPR == RO_SUM && T != DT_INT32) {
-            if (f.group) {
-                fold_vectors<T, OPR, REQ, TREE, false, MEM, true>(f, 0, n, lane);
-                return;
-            }
+__device__ __forceinline__ void fold_tile(const Fold1& f, uint32_t n, bool aligned, uint32_t lane) {
+    if constexpr (!TREE && OPR == RO_SUM && T != DT_INT32) {
+        if (f.group) {
+            if (aligned) fold_vectors<T, OPR, REQ, TREE, false, MEM, true>(f, n, lane);
+            else fold_vectors<T, OPR, REQ, TREE, true, MEM, true>(f, n, lane);
+            return;
         }
-        fold_vectors<T, OPR, REQ, TREE, false, MEM, false>(f, 0, n, lane);
-        return;
     }
-    // Destinations that agree modulo 16: single elements up to their first 16-byte boundary, then
-    // vectors, the sources read at their element alignment. (A fold in groups goes by elements.)
-    if (!(flags & UF_DST_AGREE) || f.group) {
-        fold_elems<T, OPR, REQ, TREE>(f, 0, n, lane);
-        return;
-    }
-    uint32_t head = (uint32_t)(16u - ((uint64_t)f.dest(0) & 15u)) % 16u / DtInfo<T>::size;
-    if (head > n) head = n;
-    if (head) fold_elems<T, OPR, REQ, TREE>(f, 0, head, lane);
-    fold_vectors<T, OPR, REQ, TREE, true, MEM, false>(f, head, n, lane);
+    if (aligned) fold_vectors<T, OPR, REQ, TREE, false, MEM, false>(f, n, lane);
+    else fold_vectors<T, OPR, REQ, TREE, true, MEM, false>(f, n, lane);
 }
 
 // Number of this wavefront in the launch (see hccl_executor for the XCD order).
@@ -307,17 +306,17 @@ __device__ __forceinline__ uint32_t wave_number(bool xcd_order) {
 template <int T, int MODE, bool TREE, int MEM>
 __global__ void __launch_bounds__(kBlockThreads) hccl_uniform_reduce(UniformArgs a, uint32_t redop) {
     const uint32_t lane = __lane_id();
-    const ArgList args = (ArgList)__builtin_amdgcn_kernarg_segment_ptr();
     Fold1 f;
+    f.src = lane_entry(offsetof(UniformArgs, src), lane);
+    f.dst = lane_entry(offsetof(UniformArgs, dst), lane);
     f.nsrc = a.nsrc;
     f.ndst = a.ndst;
     f.group = a.group;
-    f.src = args + offsetof(UniformArgs, src) / 8;
     for (uint32_t t = wave_number(a.flags & UF_XCD); t < a.ntiles; t += a.nworkers) {
         const uint32_t g = a.nseg > 1 ? t / a.tiles_per_seg : 0u;
         const uint32_t k = t - g * a.tiles_per_seg;
-        f.dst = args + offsetof(UniformArgs, dst) / 8 + (a.flags & UF_DST_PER_SEG ? g : 0u);
-        const uint32_t pad = a.flags & UF_ALIGNED ? 0u : line_pad(f.dst[0] + g * a.dst_step, DtInfo<T>::size);
+        f.first = a.flags & UF_DST_PER_SEG ? g : 0u;
+        const uint32_t pad = a.flags & UF_ALIGNED ? 0u : line_pad(from_lane(f.dst, f.first) + g * a.dst_step, DtInfo<T>::size);
         uint64_t e0;
         uint32_t n;
         if (!tile_range(k, a.tile_elems, pad, g + 1 < a.nseg ? a.seg_elems : a.last_elems, e0, n)) continue;
@@ -325,10 +324,10 @@ __global__ void __launch_bounds__(kBlockThreads) hccl_uniform_reduce(UniformArgs
         f.dst_off = g * a.dst_step + e0 * DtInfo<T>::size;
         f.rot = a.flags & UF_ROTATE ? (g + 1 < a.nsrc ? g + 1 : 0u) : 0u;
         f.flip = a.flags & UF_FLIP ? __brev(g) >> (__clz(a.nsrc) + 1) : 0u;
-        if constexpr (MODE == M_SUM) fold_tile<T, RO_SUM, false, TREE, MEM>(f, n, a.flags, lane);
-        else if constexpr (MODE == M_REQ) fold_tile<T, RO_SUM, true, TREE, MEM>(f, n, a.flags, lane);
-        else if (redop == RO_MAX) fold_tile<T, RO_MAX, false, TREE, MEM>(f, n, a.flags, lane);
-        else fold_tile<T, RO_MIN, false, TREE, MEM>(f, n, a.flags, lane);
+        if constexpr (MODE == M_SUM) fold_tile<T, RO_SUM, false, TREE, MEM>(f, n, a.flags & UF_ALIGNED, lane);
+        else if constexpr (MODE == M_REQ) fold_tile<T, RO_SUM, true, TREE, MEM>(f, n, a.flags & UF_ALIGNED, lane);
+        else if (redop == RO_MAX) fold_tile<T, RO_MAX, false, TREE, MEM>(f, n, a.flags & UF_ALIGNED, lane);
+        else fold_tile<T, RO_MIN, false, TREE, MEM>(f, n, a.flags & UF_ALIGNED, lane);
     }
 }
 
@@ -339,20 +338,19 @@ __global__ void __launch_bounds__(kBlockThreads) hccl_uniform_reduce(UniformArgs
 template <int ES>
 __global__ void __launch_bounds__(kBlockThreads) hccl_uniform_copy(UniformArgs a) {
     const uint32_t lane = __lane_id();
-    const ArgList args = (ArgList)__builtin_amdgcn_kernarg_segment_ptr();
-    const ArgList srcs = args + offsetof(UniformArgs, src) / 8, dsts = args + offsetof(UniformArgs, dst) / 8;
+    const uint64_t srcs = lane_entry(offsetof(UniformArgs, src), lane), dsts = lane_entry(offsetof(UniformArgs, dst), lane);
     const uint32_t sets = (a.ndst + a.per_wave - 1) / a.per_wave;
     for (uint32_t t = wave_number(false); t < a.ntiles; t += a.nworkers) {
         const uint32_t tile = sets > 1 ? t / sets : t, set = t - tile * sets;
         const uint32_t g = a.nseg > 1 ? tile / a.tiles_per_seg : 0u;
-        const uint32_t pad = a.flags & UF_ALIGNED ? 0u : line_pad(dsts[a.flags & UF_DST_PER_SEG ? g : 0u] + g * a.dst_step, ES);
+        const uint32_t pad = a.flags & UF_ALIGNED ? 0u : line_pad(from_lane(dsts, a.flags & UF_DST_PER_SEG ? g : 0u) + g * a.dst_step, ES);
         uint64_t e0;
         uint32_t n;
         if (!tile_range(tile - g * a.tiles_per_seg, a.tile_elems, pad, g + 1 < a.nseg ? a.seg_elems : a.last_elems, e0, n)) continue;
-        const char* src = (const char*)(srcs[a.flags & UF_SRC_PER_SEG ? g : 0u] + g * a.src_step + e0 * ES);
+        const char* src = (const char*)(from_lane(srcs, a.flags & UF_SRC_PER_SEG ? g : 0u) + g * a.src_step + e0 * ES);
         const uint32_t j1 = (set + 1) * a.per_wave < a.ndst ? (set + 1) * a.per_wave : a.ndst;
         for (uint32_t j = set * a.per_wave; j < j1; ++j) {
-            char* dst = (char*)(dsts[a.flags & UF_DST_PER_SEG ? g : j] + g * a.dst_step + e0 * ES);
+            char* dst = (char*)(from_lane(dsts, a.flags & UF_DST_PER_SEG ? g : j) + g * a.dst_step + e0 * ES);
             if (dst != src) copy_run<ES>(src, dst, n, lane);
         }
     }

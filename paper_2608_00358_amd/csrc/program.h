@@ -309,7 +309,6 @@ enum UniformFlags : uint32_t {
     UF_ROTATE = 4,        // segment g folds sources g + 1, g + 2, ..., nsrc - 1, 0, ..., g
     UF_FLIP = 64,         // source i of segment g is entry i with g, its bits reversed, flipped in
     UF_ALIGNED = 8,       // every operand of every tile is 16-byte aligned
-    UF_DST_AGREE = 16,    // the destinations of one segment agree modulo 16
     UF_XCD = 32,          // wavefronts numbered XCD by XCD
 };
 struct UniformArgs {
