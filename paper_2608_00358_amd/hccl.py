@@ -142,8 +142,13 @@ def _addr_or_null(x) -> Optional[int]:
     return None if x is None else _addr(x)
 
 
+_ptr_types = [ctypes.c_void_p * n for n in range(MAX_RANKS + 1)]  # making an array type costs more than filling one
+
+
 def _ptr_array(bufs: Sequence) -> ctypes.Array:
-    return (ctypes.c_void_p * len(bufs))(*[_addr(b) for b in bufs])
+    n = len(bufs)
+    kind = _ptr_types[n] if n <= MAX_RANKS else ctypes.c_void_p * n
+    return kind(*[b if isinstance(b, int) else b.data_ptr() for b in bufs])
 
 
 def _size_array(a) -> ctypes.Array:
@@ -151,26 +156,41 @@ def _size_array(a) -> ctypes.Array:
     return (ctypes.c_size_t * len(flat))(*flat)
 
 
+_torch_dtypes = {}
+
+
 def _dtype_code(dtype) -> int:
     if isinstance(dtype, str):
         return DTYPES[dtype]
     if isinstance(dtype, int):
         return dtype
-    import torch
+    if not _torch_dtypes:
+        import torch
 
-    table = {torch.bfloat16: 0, torch.float16: 1, torch.float32: 2, torch.int32: 3}
-    if dtype not in table:
+        _torch_dtypes.update({torch.bfloat16: 0, torch.float16: 1, torch.float32: 2, torch.int32: 3})
+    code = _torch_dtypes.get(dtype)
+    if code is None:
         raise TypeError(f"unsupported element type {dtype}")
-    return table[dtype]
+    return code
+
+
+_current_stream = None  # torch's query of the current stream, once a GPU has been seen
 
 
 def _stream_handle(stream) -> Optional[int]:
     if stream is None:
-        import torch
+        global _current_stream
+        if _current_stream is None:
+            import torch
 
-        if torch.cuda.is_available():
-            return torch.cuda.current_stream().cuda_stream
-        return None
+            if not torch.cuda.is_available():
+                return None
+            raw = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+            if raw is not None:  # the same handle without a Stream object around it
+                _current_stream = lambda: raw(torch.cuda.current_device())  # noqa: E731
+            else:
+                _current_stream = lambda: torch.cuda.current_stream().cuda_stream  # noqa: E731
+        return _current_stream()
     if isinstance(stream, int):
         return stream
     return stream.cuda_stream
