@@ -29,6 +29,7 @@
 namespace hccl {
 hipError_t launch_executor(const LaunchArgs& a, uint32_t blocks, int kind, hipStream_t stream);
 hipError_t launch_uniform(const UniformKernel& k, const UniformArgs& a, uint32_t blocks, hipStream_t stream);
+hipError_t launch_copy_list(const CopyListArgs& a, uint32_t blocks, hipStream_t stream);
 uint32_t dynamic_waves_per_block(uint32_t P);
 hipError_t launch_dynamic(const DynamicArgs& a, uint32_t elem_bytes, uint32_t blocks, hipStream_t stream);
 hipError_t launch_fill_u32(uint32_t* p, uint64_t n, uint32_t v, hipStream_t stream);
@@ -640,6 +641,21 @@ hipError_t launch_uniform_phase(const hcclComm* c, const UniformPhase& u, char* 
     return launch_uniform(u.kernel, a, blocks, s);
 }
 
+// Launches a program's copy list, one wavefront per tile.
+hipError_t launch_list(const hcclComm* c, const HostProgram& prog, const LaunchArgs& l, hipStream_t s, uint32_t& workers) {
+    CopyListArgs a;
+    a.list = l.prog + prog.list_offset;
+    a.nentry = prog.list_entries;
+    a.ntiles = prog.list_tiles;
+    std::memcpy(a.bufs, l.bufs, sizeof a.bufs);
+    const uint32_t wpb = (uint32_t)executor_waves_per_block();
+    workers = std::min<uint32_t>(a.ntiles, kMaxGridWorkers);
+    if (c->cfg.max_workers > 0) workers = std::min<uint32_t>(workers, (uint32_t)c->cfg.max_workers);
+    const uint32_t blocks = (workers + wpb - 1) / wpb;
+    a.nworkers = workers = blocks * wpb;
+    return launch_copy_list(a, blocks, s);
+}
+
 // Program description for hccl_comm_last_program.
 void describe(hcclProgramInfo_t& info, const std::vector<CollectiveSpec>& specs, const HostProgram& prog, bool hit,
               double compile_us) {
@@ -810,6 +826,10 @@ hcclResult_t run_packet(hcclComm* c, const std::vector<Call>& calls) {
             e = launch_lone_dynamic(c, calls[0], s, a.nworkers);
             if (e != hipSuccess) return hip_fail(e, "dynamic launch");
             hlog(c, 3, "launched from the launch packet: %u wavefronts", a.nworkers);
+        } else if (packed && dp->prog.list_entries > 0) {
+            e = launch_list(c, dp->prog, a, s, a.nworkers);
+            if (e != hipSuccess) return hip_fail(e, "copy list launch");
+            hlog(c, 3, "launched the copy list: %u entries, %u wavefronts", dp->prog.list_entries, a.nworkers);
         } else if (packed && dp->prog.uniform[q].ok) {
             e = launch_uniform_phase(c, dp->prog.uniform[q], a.bufs, s, a.nworkers);
             if (e != hipSuccess) return hip_fail(e, "uniform launch");

@@ -1226,6 +1226,42 @@ UniformPhase find_uniform(const std::vector<HostDesc>& all, uint32_t d0, uint32_
     return u;
 }
 
+// The copy list of a program of one phase (see CopyEntry), destination by destination, the calls of a
+// group in the order of its steps: at any moment the chip fills one receive buffer in order. Empty
+// if the program is not of that form.
+std::vector<CopyEntry> copy_list(const HostProgram& p, uint32_t& ntiles) {
+    std::vector<CopyEntry> list;
+    std::unordered_map<uint32_t, size_t> first;  // destination buffer -> its first step
+    struct Piece { size_t first; CopyEntry e; };
+    std::vector<Piece> v;
+    for (size_t i = 0; i < p.descs.size(); ++i) {
+        const HostDesc& d = p.descs[i];
+        if (d.op != OP_COPY || d.srcs.size() != 1 || d.dsts.size() != 1 || !d.deps.empty() || d.nelem == 0) return list;
+        if (d.srcs[0].buf >= 2u * kMaxRanks || d.dsts[0].buf >= 2u * kMaxRanks) return list;
+        first.emplace(d.dsts[0].buf, i);
+        v.push_back({first[d.dsts[0].buf], {d.srcs[0].offset, d.dsts[0].offset, d.nelem * dtype_size(d.srcs[0].dtype),
+                                            d.srcs[0].buf | d.dsts[0].buf << 16, 0}});
+    }
+    std::sort(v.begin(), v.end(), [](const Piece& a, const Piece& b) {
+        return a.first != b.first ? a.first < b.first : a.e.dst_off < b.e.dst_off;
+    });
+    for (const Piece& c : v) {
+        if (!list.empty() && list.back().bufs == c.e.bufs && list.back().src_off + list.back().bytes == c.e.src_off &&
+            list.back().dst_off + list.back().bytes == c.e.dst_off)
+            list.back().bytes += c.e.bytes;
+        else
+            list.push_back(c.e);
+    }
+    uint64_t t = 0;
+    for (CopyEntry& e : list) {
+        e.tile0 = (uint32_t)t;
+        t += (e.bytes + kListTileBytes - 1) / kListTileBytes;
+    }
+    if (list.size() > kListMaxEntries || t >= (1ull << 31)) list.clear();
+    ntiles = (uint32_t)t;
+    return list;
+}
+
 }  // namespace
 
 // ---------------------------------------------------------------------------- packing
@@ -1482,7 +1518,18 @@ bool finalize(HostProgram& p, uint32_t tile_bytes, std::string& err) {
     hdr.naux = (uint32_t)p.aux.size();
     hdr.nphase = nphase;
     hdr.off_phase = align16(hdr.off_aux + p.aux.size() * sizeof(DynA2A));
-    hdr.total_bytes = align16(hdr.off_phase + p.phase_tile.size() * sizeof(uint32_t));
+    const uint64_t off_list = align16(hdr.off_phase + p.phase_tile.size() * sizeof(uint32_t));
+    std::vector<CopyEntry> list;
+    if (nphase == 1 && !tile_bytes && !p.uniform[0].ok) list = copy_list(p, p.list_tiles);
+    p.list_entries = (uint32_t)list.size();
+    std::vector<uint32_t> ends;
+    if (!list.empty()) {
+        p.list_offset = hdr.off_list = off_list;
+        ends.assign(64 + (list.size() + 63) / 64 * 64, ~0u);
+        for (size_t i = 0; i < list.size(); ++i)
+            ends[64 + i] = ends[i / 64] = i + 1 < list.size() ? list[i + 1].tile0 : p.list_tiles;
+    }
+    hdr.total_bytes = off_list + ends.size() * sizeof(uint32_t) + list.size() * sizeof(CopyEntry);
     hdr.scratch_bytes = p.scratch_bytes;
     p.image.assign(hdr.total_bytes, 0);
     std::memcpy(p.image.data(), &hdr, sizeof hdr);
@@ -1492,6 +1539,10 @@ bool finalize(HostProgram& p, uint32_t tile_bytes, std::string& err) {
     if (!tile_owner.empty())
         std::memcpy(p.image.data() + hdr.off_tile_desc, tile_owner.data(), tile_owner.size() * sizeof(uint32_t));
     if (!p.aux.empty()) std::memcpy(p.image.data() + hdr.off_aux, p.aux.data(), p.aux.size() * sizeof(DynA2A));
+    if (!list.empty()) {
+        std::memcpy(p.image.data() + off_list, ends.data(), ends.size() * sizeof(uint32_t));
+        std::memcpy(p.image.data() + off_list + ends.size() * sizeof(uint32_t), list.data(), list.size() * sizeof(CopyEntry));
+    }
     std::memcpy(p.image.data() + hdr.off_phase, p.phase_tile.data(), p.phase_tile.size() * sizeof(uint32_t));
     return true;
 }

@@ -133,6 +133,9 @@ struct HostProgram {
     std::vector<int> phase_kind;
     std::vector<uint8_t> phase_xcd;  // 1 = the phase's wavefronts are numbered XCD by XCD
     std::vector<UniformPhase> uniform;  // one per phase
+    uint32_t list_entries = 0;          // copy list in the image (0: none) and its tiles
+    uint32_t list_tiles = 0;
+    uint64_t list_offset = 0;
     uint32_t nphase() const { return phase_kind.empty() ? 1u : (uint32_t)phase_kind.size(); }
 };
 

@@ -191,7 +191,7 @@ struct ProgramHeader {
     uint32_t naux;
     uint32_t nphase;       // phases (launches) of the program, 1 .. kMaxPhases
     uint64_t off_phase;    // nphase + 1 u32 tile numbers: phase p runs tiles [t[p], t[p+1])
-    uint64_t pad;
+    uint64_t off_list;     // the copy list, or 0 (CopyEntry)
 };
 static_assert(sizeof(ProgramHeader) % 16 == 0, "arrays follow the header 16-byte aligned");
 
@@ -347,6 +347,29 @@ struct DynamicArgs {
     uint32_t pad;
     uint64_t send[kMaxRanks];
     uint64_t recv[kMaxRanks];
+};
+
+// Copy list of a program that is nothing but copies of one source to one destination (an AllToAllv, or
+// a group of them): the same copies as its steps, joined where they continue one another, for a
+// kernel that finds a tile's copy by its tile number. In the image at off_list: the tiles up to and
+// with every 64th entry (64 words), the tiles up to and with every entry (a multiple of 64 words,
+// filled up with ~0), then the entries.
+constexpr uint32_t kListTileBytes = 4096;
+constexpr uint32_t kListMaxEntries = 64 * 64;
+struct CopyEntry {         // 32 bytes
+    uint64_t src_off;      // bytes into the buffers
+    uint64_t dst_off;
+    uint64_t bytes;
+    uint32_t bufs;         // source buffer id | destination buffer id << 16
+    uint32_t tile0;        // first tile
+};
+struct CopyListArgs {
+    const uint8_t* list;
+    uint32_t nentry;
+    uint32_t ntiles;
+    uint32_t nworkers;
+    uint32_t pad;
+    char* bufs[2 * kMaxRanks];
 };
 
 // Data accesses of a uniform phase that are ordinary ones; the others are non-temporal.

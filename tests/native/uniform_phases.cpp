@@ -91,9 +91,83 @@ Writes from_uniform(const UniformPhase& u, uint64_t pad, const char* what) {
     return w;
 }
 
+// The copies of a program's list, found tile by tile as the kernel finds them, in 2-byte units.
+Writes from_list(const HostProgram& p, const char* what) {
+    Writes w;
+    const uint8_t* base = p.image.data() + p.list_offset;
+    const uint32_t* ends = (const uint32_t*)base;
+    const uint32_t n = p.list_entries;
+    const CopyEntry* entries = (const CopyEntry*)(base + 256 + 256 * ((n + 63) / 64));
+    for (uint32_t t = 0; t < p.list_tiles; ++t) {
+        uint32_t b = 0, i = 0;
+        if (n > 64)
+            for (uint32_t l = 0; l < 64; ++l) b += ends[l] <= t;
+        for (uint32_t l = 0; l < 64; ++l) i += ends[64 + 64 * b + l] <= t;
+        const CopyEntry& e = entries[64 * b + i];
+        const uint64_t pad = (t - e.tile0) ? 10 : 0;  // tile 0 takes 10 units more, the others start later
+        const uint64_t first = (uint64_t)(t - e.tile0) * (kListTileBytes / 2) + pad;
+        const uint64_t most = kListTileBytes / 2 + (t == e.tile0 ? 10 : 0);
+        for (uint64_t k = first; k < first + most && k < e.bytes / 2; ++k)
+            write(w, {e.bufs >> 16, e.dst_off + 2 * k}, {e.bufs & 0xFFFFu, e.src_off + 2 * k}, what);
+    }
+    return w;
+}
+
+Writes halves_of_steps(const HostProgram& p, const char* what) {
+    Writes w;
+    for (const HostDesc& d : p.descs)
+        for (uint64_t k = 0; k < d.nelem * dtype_size(d.srcs[0].dtype) / 2; ++k)
+            write(w, {d.dsts[0].buf, d.dsts[0].offset + 2 * k}, {d.srcs[0].buf, d.srcs[0].offset + 2 * k}, what);
+    return w;
+}
+
+CollectiveSpec exchange(int P, int dtype, uint64_t rows, uint64_t width, uint64_t chunk, uint32_t seed) {
+    CollectiveSpec s;
+    s.coll = COLL_ALLTOALLV;
+    s.P = P;
+    s.dtype = dtype;
+    s.chunk_bytes = chunk;
+    s.sendcounts.resize(P * P), s.sdispls.resize(P * P), s.recvcounts.resize(P * P), s.rdispls.resize(P * P);
+    auto next = [&] { return (seed = seed * 1664525u + 1013904223u) >> 8; };
+    for (int i = 0; i < P * P; ++i) s.sendcounts[i] = next() % 3 ? next() % (rows + 1) * width : 0;
+    for (int a = 0; a < P; ++a) {
+        uint64_t so = next() % 3, ro = next() % 3;
+        for (int b = 0; b < P; ++b) {
+            s.sdispls[a * P + b] = so, so += s.sendcounts[a * P + b] + (b % 2);
+            s.recvcounts[a * P + b] = s.sendcounts[b * P + a];
+            s.rdispls[a * P + b] = ro, ro += s.recvcounts[a * P + b] + (a % 2);
+        }
+    }
+    return s;
+}
+
+void lists() {
+    for (int P : {1, 2, 8, 9, 24})
+        for (uint64_t chunk : {uint64_t(0), uint64_t(512)})
+            for (int grouped = 0; grouped < 2; ++grouped) {
+                const std::string what = "exchange P " + std::to_string(P) + " chunk " + std::to_string(chunk) + " grouped " + std::to_string(grouped);
+                std::vector<CollectiveSpec> specs{exchange(P, DT_BF16, 9, P < 9 ? 701 : 5, chunk, P)};
+                if (grouped) specs.push_back(exchange(P, DT_INT32, 9, 1, chunk, P + 1));
+                std::vector<HostProgram> parts(specs.size());
+                std::string err;
+                for (size_t k = 0; k < specs.size(); ++k) lower(specs[k], parts[k], err), fuse(parts[k]);
+                HostProgram p;
+                if (grouped) merge(parts, specs, p, err);
+                else p = parts[0];
+                finalize(p, 0, err);
+                ++programs;
+                if (p.descs.empty() || p.uniform[0].ok) continue;
+                if (!p.list_entries || from_list(p, what.c_str()) != halves_of_steps(p, what.c_str())) {
+                    std::printf("LIST DIFFERS %s\n", what.c_str());
+                    ++bad;
+                }
+            }
+}
+
 }  // namespace
 
 int main() {
+    lists();
     const int algos[] = {ALGO_AUTO, ALGO_DIRECT, ALGO_RING, ALGO_RHD, ALGO_TWO_LEVEL};
     struct Shape { int P; uint64_t count; };
     const Shape shapes[] = {{1, 5}, {2, 1}, {2, 777}, {3, 700}, {4, 129}, {8, 300}, {8, 8 * 64}, {16, 70}, {64, 3}};
