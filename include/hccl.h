@@ -205,9 +205,9 @@ hcclResult_t hccl_allreduce(hcclComm_t comm, const void* const* sendbufs, void* 
  * program image, dependency counters and FP32 partials live in a static workspace of 64 MiB
  * that the library holds on every device it runs on until the process ends; the call makes no
  * hipMalloc, hipFree or other device allocation (its program is compiled, and cached, in host
- * memory). On `stream` it copies the program into the workspace, clears the counters with a
- * fill kernel and launches the executor (a one-step program goes in the launch packet and does
- * not touch the workspace). The communicator must have a device (its error record, allocated
+ * memory). On `stream` it copies the program into the workspace, clears the counters of a
+ * program that waits on the device with a fill kernel, and launches the executor (a program
+ * that travels in its launch packets does not touch the workspace). The communicator must have a device (its error record, allocated
  * by hccl_comm_create, is used); the inputs and outputs are the caller's as usual.
  * Every call on one device shares that workspace and finds it as the last call left it: calls
  * whose work can overlap in time on one GPU (other streams, other communicators) race, and the
@@ -403,7 +403,7 @@ typedef struct {
     uint32_t num_operands;       /* operand entries */
     uint32_t workers;            /* wavefronts of the last launch (0 on host-only comms) */
     uint32_t max_srcs;           /* most sources of one step */
-    uint32_t inline_launch;      /* 1 if the one-step program travelled in the launch packet */
+    uint32_t inline_launch;      /* 1 if the whole program travelled in its launch packets */
     uint32_t tickets;            /* 1 if the last launch handed out tiles by atomic ticket (dependent
                                     programs by default; see HCCL_DISPATCH), 0 if statically */
     uint64_t bytes_read;         /* bytes the program's steps read */
@@ -437,8 +437,8 @@ hcclResult_t hccl_comm_program_image(hcclComm_t comm, void* out, size_t capacity
  * component handled it; the control-core overhead is read off them). With hcclConfig_t.trace
  * set, every launch records, for each tile of its program, the wall-clock time at which an
  * executor wavefront took it, how long its dependency waits lasted, when its data had moved
- * and its signals were set, and where it ran. One-step programs then also run from a device
- * image instead of the launch packet. Launches under graph capture and resident packets are
+ * and its signals were set, and where it ran. Every program then runs from its device image
+ * instead of the launch packet. Launches under graph capture and resident packets are
  * not traced.
  */
 typedef struct {

@@ -1393,8 +1393,12 @@ bool finalize(HostProgram& p, uint32_t tile_bytes, std::string& err) {
         d.nsrc = (uint16_t)h.srcs.size();
         d.ndst = (uint16_t)h.dsts.size();
         d.nelem = h.nelem;
-        d.fold = h.fold;
-        d.requant = h.requant ? 1u : 0u;
+        // A maximum, a minimum and a wrapping sum do not depend on how their list is bracketed (ties
+        // and NaNs keep the first in list order), and only 16-bit sums round their partials: the
+        // kernels have trees and re-quantised folds for sums alone.
+        const bool sum = h.op == OP_REDUCE && h.redop == RO_SUM, wide = !h.dsts.empty() && dtype_size(h.dsts[0].dtype) == 4;
+        d.fold = sum && h.dsts[0].dtype != DT_INT32 ? h.fold : (uint32_t)FOLD_LIST;
+        d.requant = sum && !wide && h.requant ? 1u : 0u;
         const uint64_t dte = step_tile(h, p.desc_phase[i]);
         d.tile_elems = (uint32_t)dte;
         if (h.op == OP_COPY || h.op == OP_REDUCE) {

@@ -575,30 +575,24 @@ __device__ __forceinline__ void reduce_dispatch_op(uint32_t op, const TileOps& t
     }
 }
 
+// (the compiler leaves the tree to floating sums: see finalize)
 template <int T>
-__device__ __forceinline__ void run_tree(uint32_t op, const TileOps& t, uint32_t n, bool aligned, uint32_t lane) {
-    if (op == RO_SUM) {
-        if constexpr (T == DT_BF16 || T == DT_FP16) {
-            if (t.requant) {
-                reduce_tile_tree<T, RO_SUM, true>(t, n, aligned, lane);
-                return;
-            }
+__device__ __forceinline__ void run_tree(const TileOps& t, uint32_t n, bool aligned, uint32_t lane) {
+    if constexpr (T == DT_BF16 || T == DT_FP16) {
+        if (t.requant) {
+            reduce_tile_tree<T, RO_SUM, true>(t, n, aligned, lane);
+            return;
         }
-        reduce_tile_tree<T, RO_SUM, false>(t, n, aligned, lane);
-    } else if (op == RO_MAX) {
-        reduce_tile_tree<T, RO_MAX, false>(t, n, aligned, lane);
-    } else {
-        reduce_tile_tree<T, RO_MIN, false>(t, n, aligned, lane);
     }
+    reduce_tile_tree<T, RO_SUM, false>(t, n, aligned, lane);
 }
 
 __device__ __forceinline__ void run_reduce(uint32_t sig, uint32_t op, const TileOps& t, uint32_t n, bool aligned, uint32_t lane) {
     if (t.fold == FOLD_PAIRWISE) {
         switch (sig) {
-            case SIG_BF16: run_tree<DT_BF16>(op, t, n, aligned, lane); break;
-            case SIG_FP16: run_tree<DT_FP16>(op, t, n, aligned, lane); break;
-            case SIG_FP32: run_tree<DT_FP32>(op, t, n, aligned, lane); break;
-            case SIG_INT32: run_tree<DT_INT32>(op, t, n, aligned, lane); break;
+            case SIG_BF16: run_tree<DT_BF16>(t, n, aligned, lane); break;
+            case SIG_FP16: run_tree<DT_FP16>(t, n, aligned, lane); break;
+            case SIG_FP32: run_tree<DT_FP32>(t, n, aligned, lane); break;
             default: break;
         }
         return;
