@@ -13,6 +13,7 @@
 
 #include <algorithm>
 #include <cstring>
+#include <list>
 #include <unordered_map>
 
 namespace hccl {
@@ -1081,7 +1082,15 @@ UniformPhase find_uniform(const std::vector<HostDesc>& all, uint32_t d0, uint32_
     if (f.srcs.empty() || f.dsts.empty()) return u;
     const uint32_t dt = f.srcs[0].dtype;
     const uint64_t es = dtype_size(dt);
-    std::vector<HostDesc> steps;
+    struct Step {
+        const std::vector<Operand>* srcs;
+        const std::vector<Operand>* dsts;
+        uint64_t nelem;
+        uint64_t bufs;  // a hash of the buffers named, so that steps of the same ones sort together
+    };
+    std::vector<Step> steps;
+    std::list<std::vector<Operand>> sorted;  // the order of a step's destinations is free
+    auto by_buf = [](const Operand& a, const Operand& b) { return a.buf < b.buf; };
     for (uint32_t i = d0; i < d1; ++i) {
         const HostDesc& d = all[i];
         if (d.op != f.op || d.redop != f.redop || d.group != f.group || d.fold != f.fold || d.requant != f.requant ||
@@ -1090,110 +1099,113 @@ UniformPhase find_uniform(const std::vector<HostDesc>& all, uint32_t d0, uint32_
         for (const auto* list : {&d.srcs, &d.dsts})
             for (const Operand& o : *list)
                 if (o.dtype != dt) return u;
-        steps.push_back(d);
+        const std::vector<Operand>* dsts = &d.dsts;
+        if (!std::is_sorted(d.dsts.begin(), d.dsts.end(), by_buf)) {
+            sorted.push_back(d.dsts);
+            std::sort(sorted.back().begin(), sorted.back().end(), by_buf);
+            dsts = &sorted.back();
+        }
+        uint64_t bufs = 0;
+        for (const auto* list : {&d.srcs, dsts})
+            for (const Operand& o : *list) bufs = (bufs ^ o.buf) * 0x9E3779B97F4A7C15ull + 1;
+        steps.push_back({&d.srcs, dsts, d.nelem, bufs});
     }
-    for (HostDesc& d : steps)  // the order of a step's destinations is free
-        std::sort(d.dsts.begin(), d.dsts.end(), [](const Operand& a, const Operand& b) { return a.buf < b.buf; });
     // join the steps that continue one another in every operand
-    auto bufs_less = [](const std::vector<Operand>& a, const std::vector<Operand>& b) {
-        return std::lexicographical_compare(a.begin(), a.end(), b.begin(), b.end(),
-                                            [](const Operand& x, const Operand& y) { return x.buf < y.buf; });
-    };
-    std::stable_sort(steps.begin(), steps.end(), [&](const HostDesc& a, const HostDesc& b) {
-        if (!same_bufs(a.srcs, b.srcs)) return bufs_less(a.srcs, b.srcs);
-        if (!same_bufs(a.dsts, b.dsts)) return bufs_less(a.dsts, b.dsts);
-        return a.dsts[0].offset < b.dsts[0].offset;
+    std::stable_sort(steps.begin(), steps.end(), [](const Step& a, const Step& b) {
+        return a.bufs != b.bufs ? a.bufs < b.bufs : (*a.dsts)[0].offset < (*b.dsts)[0].offset;
     });
-    std::vector<HostDesc> segs;
-    for (HostDesc& d : steps) {
-        bool joins = !segs.empty() && same_bufs(segs.back().srcs, d.srcs) && same_bufs(segs.back().dsts, d.dsts);
+    std::vector<Step> segs;
+    for (const Step& d : steps) {
+        bool joins = !segs.empty() && same_bufs(*segs.back().srcs, *d.srcs) && same_bufs(*segs.back().dsts, *d.dsts);
         if (joins) {
-            const HostDesc& p = segs.back();
-            for (size_t k = 0; k < d.srcs.size(); ++k) joins &= d.srcs[k].offset == p.srcs[k].offset + p.nelem * es;
-            for (size_t k = 0; k < d.dsts.size(); ++k) joins &= d.dsts[k].offset == p.dsts[k].offset + p.nelem * es;
+            const Step& p = segs.back();
+            for (size_t k = 0; k < d.srcs->size(); ++k) joins &= (*d.srcs)[k].offset == (*p.srcs)[k].offset + p.nelem * es;
+            for (size_t k = 0; k < d.dsts->size(); ++k) joins &= (*d.dsts)[k].offset == (*p.dsts)[k].offset + p.nelem * es;
         }
         if (joins) segs.back().nelem += d.nelem;
-        else segs.push_back(std::move(d));
+        else segs.push_back(d);
         if (segs.size() > (size_t)kMaxOperands) return u;
     }
-    std::stable_sort(segs.begin(), segs.end(), [](const HostDesc& a, const HostDesc& b) {
-        if (a.dsts[0].offset != b.dsts[0].offset) return a.dsts[0].offset < b.dsts[0].offset;
-        if (a.srcs[0].offset != b.srcs[0].offset) return a.srcs[0].offset < b.srcs[0].offset;
-        return a.srcs[0].buf < b.srcs[0].buf;
+    std::stable_sort(segs.begin(), segs.end(), [](const Step& a, const Step& b) {
+        const Operand &ad = (*a.dsts)[0], &bd = (*b.dsts)[0], &as = (*a.srcs)[0], &bs = (*b.srcs)[0];
+        if (ad.offset != bd.offset) return ad.offset < bd.offset;
+        if (as.offset != bs.offset) return as.offset < bs.offset;
+        return as.buf < bs.buf;
     });
-    const HostDesc& s0 = segs[0];
+    const Step& s0 = segs[0];
+    const std::vector<Operand>& src0 = *s0.srcs;
+    const std::vector<Operand>& dst0 = *s0.dsts;
     const uint32_t n = (uint32_t)segs.size();
     for (uint32_t g = 1; g < n; ++g)
         if (g + 1 < n ? segs[g].nelem != s0.nelem : segs[g].nelem > s0.nelem) return u;
 
     // one list for every segment, at a constant step?
-    auto shared = [&](std::vector<Operand> HostDesc::*list, uint64_t& step) {
-        const auto& base = s0.*list;
-        step = n > 1 ? (segs[1].*list)[0].offset - base[0].offset : 0;
+    auto shared = [&](const std::vector<Operand>* Step::*list, uint64_t& step) {
+        const std::vector<Operand>& base = *(s0.*list);
+        step = n > 1 ? (*(segs[1].*list))[0].offset - base[0].offset : 0;
         for (uint32_t g = 1; g < n; ++g) {
-            if (!same_bufs(segs[g].*list, base)) return false;
+            if (!same_bufs(*(segs[g].*list), base)) return false;
             for (size_t k = 0; k < base.size(); ++k)
-                if ((segs[g].*list)[k].offset != base[k].offset + g * step) return false;
+                if ((*(segs[g].*list))[k].offset != base[k].offset + g * step) return false;
         }
         return true;
     };
     // the sources of segment g are those of one list from its place g + 1 on (ring order)?
     auto rotated = [&](uint64_t step, std::vector<Operand>& base) {
-        const uint32_t m = (uint32_t)s0.srcs.size();
+        const uint32_t m = (uint32_t)src0.size();
         base.resize(m);
-        for (uint32_t k = 0; k < m; ++k) base[(k + 1) % m] = s0.srcs[k];
+        for (uint32_t k = 0; k < m; ++k) base[(k + 1) % m] = src0[k];
         for (uint32_t g = 0; g < n; ++g)
             for (uint32_t k = 0; k < m; ++k) {
-                const Operand &o = base[(k + g + 1) % m], &x = segs[g].srcs[k];
+                const Operand &o = base[(k + g + 1) % m], &x = (*segs[g].srcs)[k];
                 if (x.buf != o.buf || x.offset != o.offset + g * step) return false;
             }
         return n <= m;
     };
     // ... or those of segment 0 with the bits of g, in reverse, flipped in their place (halving order)?
     auto flipped = [&](uint64_t step) {
-        const uint32_t m = (uint32_t)s0.srcs.size();
+        const uint32_t m = (uint32_t)src0.size();
         if ((m & (m - 1)) != 0 || n > m) return false;
         for (uint32_t g = 0; g < n; ++g) {
             uint32_t rev = 0;
             for (uint32_t b = 1, t = m >> 1; b < m; b <<= 1, t >>= 1)
                 if (g & b) rev |= t;
             for (uint32_t k = 0; k < m; ++k) {
-                const Operand &o = s0.srcs[k ^ rev], &x = segs[g].srcs[k];
+                const Operand &o = src0[k ^ rev], &x = (*segs[g].srcs)[k];
                 if (x.buf != o.buf || x.offset != o.offset + g * step) return false;
             }
         }
         return true;
     };
     std::vector<Operand> base;
-    if (shared(&HostDesc::srcs, u.src_step)) {
-        u.srcs = s0.srcs;
-    } else if (s0.srcs.size() == 1) {
+    if (shared(&Step::srcs, u.src_step)) {
+        u.srcs = src0;
+    } else if (src0.size() == 1) {
         u.flags |= UF_SRC_PER_SEG;
         u.src_step = 0;
-        for (const HostDesc& d : segs) u.srcs.push_back(d.srcs[0]);
-    } else if (rotated(u.src_step = segs[1].srcs[0].offset - s0.srcs[0].offset, base)) {
+        for (const Step& d : segs) u.srcs.push_back((*d.srcs)[0]);
+    } else if (rotated(u.src_step = (*segs[1].srcs)[0].offset - src0[0].offset, base)) {
         u.flags |= UF_ROTATE;
         u.srcs = base;
     } else if (flipped(u.src_step)) {
         u.flags |= UF_FLIP;
-        u.srcs = s0.srcs;
+        u.srcs = src0;
     } else {
         return u;
     }
-    if (shared(&HostDesc::dsts, u.dst_step)) {
-        u.dsts = s0.dsts;
-    } else if (s0.dsts.size() == 1) {
+    if (shared(&Step::dsts, u.dst_step)) {
+        u.dsts = dst0;
+    } else if (dst0.size() == 1) {
         u.flags |= UF_DST_PER_SEG;
         u.dst_step = 0;
-        for (const HostDesc& d : segs) u.dsts.push_back(d.dsts[0]);
-    } else if (f.op == OP_COPY && s0.dsts.size() < (size_t)kMaxOperands) {
+        for (const Step& d : segs) u.dsts.push_back((*d.dsts)[0]);
+    } else if (f.op == OP_COPY && dst0.size() < (size_t)kMaxOperands) {
         // copies of one location of every buffer but the source's own (the results of a two-level
         // all-reduce): the list of all of them; a wavefront leaves out the destination that is
         // its source
-        auto with_source = [](const HostDesc& d) {
-            std::vector<Operand> v = d.dsts;
-            v.push_back(d.srcs[0]);
-            std::sort(v.begin(), v.end(), [](const Operand& a, const Operand& b) { return a.buf < b.buf; });
+        auto with_source = [&](const Step& d) {
+            std::vector<Operand> v = *d.dsts;
+            v.insert(std::upper_bound(v.begin(), v.end(), (*d.srcs)[0], by_buf), (*d.srcs)[0]);
             return v;
         };
         u.dsts = with_source(s0);
@@ -1212,7 +1224,7 @@ UniformPhase find_uniform(const std::vector<HostDesc>& all, uint32_t d0, uint32_
     u.seg_elems = s0.nelem;
     u.last_elems = segs[n - 1].nelem;
     uint64_t total = 0;
-    for (const HostDesc& d : segs) total += d.nelem;
+    for (const Step& d : segs) total += d.nelem;
     u.kernel = {f.op, (uint8_t)dt, f.redop, (uint8_t)f.fold, f.requant, 0};
     // (a maximum, a minimum and a wrapping sum do not depend on how their list is bracketed)
     if (f.op == OP_REDUCE && (f.redop != RO_SUM || dt == DT_INT32)) u.kernel.fold = FOLD_LIST, u.group = 0;
