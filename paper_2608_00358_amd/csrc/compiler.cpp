@@ -1051,6 +1051,10 @@ constexpr uint64_t kUniformCachedBytes = 8ull << 20;
 // 64 ranks, executor / uniform: 32 MiB per rank 719 / 750 us for the call, 8 MiB 183 / 176.
 constexpr uint64_t kLongRunDsts = 32;
 constexpr uint64_t kLongRunBytes = 16ull << 20;
+// So does one large copy by itself (one rank, 1 GiB: executor 355 us, uniform 370, as a list 360).
+bool one_long_copy(uint32_t op, uint32_t nseg, uint32_t ndst, uint64_t bytes) {
+    return op == OP_COPY && nseg == 1 && ndst == 1 && bytes >= kLongRunBytes;
+}
 
 void uniform_tile(UniformPhase& u, uint64_t elems) {
     const uint64_t es = dtype_size(u.kernel.dtype);
@@ -1240,7 +1244,8 @@ UniformPhase find_uniform(const std::vector<HostDesc>& all, uint32_t d0, uint32_
     u.per_wave = 1;
     if (tile) u.tile_elems = tile;
     else uniform_tile(u, total);
-    u.ok = u.ntiles() < (1ull << 31) && !(f.op == OP_COPY && u.ndst() >= kLongRunDsts && total * es >= kLongRunBytes);
+    u.ok = u.ntiles() < (1ull << 31) && !(f.op == OP_COPY && u.ndst() >= kLongRunDsts && total * es >= kLongRunBytes) &&
+           !one_long_copy(f.op, u.nseg, u.ndst(), total * es);
     return u;
 }
 
@@ -1275,7 +1280,8 @@ std::vector<CopyEntry> copy_list(const HostProgram& p, uint32_t& ntiles) {
         e.tile0 = (uint32_t)t;
         t += (e.bytes + kListTileBytes - 1) / kListTileBytes;
     }
-    if (list.size() > kListMaxEntries || t >= (1ull << 31)) list.clear();
+    if (list.size() > kListMaxEntries || t >= (1ull << 31) || (list.size() == 1 && one_long_copy(OP_COPY, 1, 1, list[0].bytes)))
+        list.clear();
     ntiles = (uint32_t)t;
     return list;
 }
