@@ -18,6 +18,7 @@ from __future__ import annotations
 
 import argparse
 import ctypes
+import glob
 import hashlib
 import json
 import os
@@ -1089,8 +1090,11 @@ def traffic_record(kernel: str):
         rec = json.load(open(path))
     except ValueError:
         return None
-    src = os.path.join(ROOT, "paper_2608_00358_amd", "csrc", "executor.hip")
-    digest = hashlib.sha256(open(src, "rb").read()).hexdigest()[:16]
+    digest = hashlib.sha256()
+    for src in sorted(glob.glob(os.path.join(ROOT, "paper_2608_00358_amd", "csrc", "executor*"))):
+        with open(src, "rb") as f:
+            digest.update(f.read())
+    digest = digest.hexdigest()[:16]
     entry = rec.get(kernel)
     if not entry or entry.get("executor_sha256_16") != digest:
         return None
@@ -1226,7 +1230,7 @@ def main():
                    "host_enqueue_us_per_step": round(head["host_enqueue_us"], 2)},
         "roofline": {"bound": "hbm", "achieved": round(achieved, 1), "peak": HBM_PEAK_GBS, "unit": "GB/s",
                      "frac": round(achieved / HBM_PEAK_GBS, 4), "traffic": traffic,
-                     "kernel": "hccl_executor<12> (copy-only executor; the grouped rows + ids launch)",
+                     "kernel": "hccl_copy_list (the grouped rows + ids launch)",
                      "algo_bytes_per_launch": head["algo_bytes_step"],
                      "avg_launch_us": round(head["launch_ms"] * 1e3, 2)},
     }
