@@ -495,6 +495,7 @@ void lower_alltoallv(const CollectiveSpec& s, HostProgram& p) {
         }
     }
     std::stable_sort(pieces.begin(), pieces.end(), [](const Piece& a, const Piece& c) { return a.n > c.n; });
+    p.descs.reserve(pieces.size());
     for (const Piece& pc : pieces)
         b.add(OP_COPY, RO_SUM, pc.n, {opnd(send_buf(pc.src), dt, pc.so)}, {opnd(recv_buf(P, pc.dst), dt, pc.ro)});
     p.algo = ALGO_DIRECT;
@@ -557,6 +558,19 @@ struct OperandKey {
 struct OperandKeyHash {
     size_t operator()(const OperandKey& k) const { return std::hash<uint64_t>()(k.offset * 131 + k.buf); }
 };
+
+// Scratch is needed only if some live step still touches it.
+void drop_unused_scratch(HostProgram& p) {
+    if (p.scratch_bytes == 0) return;
+    const uint32_t scratch = scratch_buf(p.P);
+    for (const HostDesc& d : p.descs) {
+        if (!d.alive) continue;
+        for (const auto* list : {&d.srcs, &d.dsts})
+            for (const Operand& o : *list)
+                if (o.buf == scratch) return;
+    }
+    p.scratch_bytes = 0;
+}
 
 }  // namespace
 
@@ -720,6 +734,12 @@ bool lower(const CollectiveSpec& s, HostProgram& p, std::string& err) {
 // them, so later lookups and dependencies resolve to the surviving step.
 void fuse(HostProgram& p) {
     const uint32_t scratch = scratch_buf(p.P);
+    p.fused = true;
+    // every rule merges a step with one that it waits for
+    if (std::none_of(p.descs.begin(), p.descs.end(), [](const HostDesc& d) { return !d.deps.empty(); })) {
+        drop_unused_scratch(p);
+        return;
+    }
     const uint32_t D = (uint32_t)p.descs.size();
     std::vector<uint32_t> fwd(D);
     for (uint32_t i = 0; i < D; ++i) fwd[i] = i;
@@ -746,6 +766,9 @@ void fuse(HostProgram& p) {
     std::vector<std::vector<uint32_t>> nread(D);
     {
         std::unordered_map<OperandKey, std::pair<uint32_t, uint32_t>, OperandKeyHash> last;
+        size_t written = 0;
+        for (const HostDesc& d : p.descs) written += d.dsts.size();
+        last.reserve(written);
         for (uint32_t i = 0; i < D; ++i) {
             const HostDesc& d = p.descs[i];
             nread[i].assign(d.dsts.size(), 0);
@@ -850,9 +873,9 @@ void fuse(HostProgram& p) {
             int64_t a = prod[i][0];
             if (private_partial(a, B) && p.descs[a].srcs.size() + B.srcs.size() - 1 <= (size_t)kMaxOperands) {
                 HostDesc& A = p.descs[a];
-                std::vector<Operand> srcs = A.srcs;
+                std::vector<Operand> srcs = std::move(A.srcs);  // A ends here
                 srcs.insert(srcs.end(), B.srcs.begin() + 1, B.srcs.end());
-                std::vector<int64_t> sprod = prod[a];
+                std::vector<int64_t> sprod = std::move(prod[a]);
                 sprod.insert(sprod.end(), prod[i].begin() + 1, prod[i].end());
                 B.srcs = std::move(srcs);
                 prod[i] = std::move(sprod);
@@ -913,15 +936,7 @@ void fuse(HostProgram& p) {
         for (Dep& e : d.deps) e.desc = find(e.desc);
         dedupe_deps(d, i);
     }
-    p.fused = true;
-    // scratch is needed only if some live step still touches it
-    bool uses_scratch = false;
-    for (const auto& d : p.descs) {
-        if (!d.alive) continue;
-        for (const Operand& o : d.srcs) uses_scratch |= (o.buf == scratch);
-        for (const Operand& o : d.dsts) uses_scratch |= (o.buf == scratch);
-    }
-    if (!uses_scratch) p.scratch_bytes = 0;
+    drop_unused_scratch(p);
 }
 
 // ------------------------------------------------------------------------------ groups
@@ -1081,6 +1096,18 @@ bool same_bufs(const std::vector<Operand>& a, const std::vector<Operand>& b) {
     return true;
 }
 
+// Operands in the order of their buffer ids (a counting sort: there are few ids).
+std::vector<Operand> by_buffer(const std::vector<Operand>& v) {
+    uint32_t most = 0;
+    for (const Operand& o : v) most = std::max(most, o.buf);
+    std::vector<uint32_t> at(most + 2, 0);
+    for (const Operand& o : v) ++at[o.buf + 1];
+    for (uint32_t b = 0; b < most; ++b) at[b + 1] += at[b];
+    std::vector<Operand> out(v.size());
+    for (const Operand& o : v) out[at[o.buf]++] = o;
+    return out;
+}
+
 // The uniform form of the steps [d0, d1) of one phase, none of which waits for another. `tile`
 // is the tile size of a configured tile_bytes (0: chosen here), which the caller asked for step
 // by step: then only a single step has this form. `reread`: a later phase reads the results.
@@ -1098,44 +1125,81 @@ UniformPhase find_uniform(const std::vector<HostDesc>& all, uint32_t d0, uint32_
         uint64_t nelem;
         uint64_t bufs;  // a hash of the buffers named, so that steps of the same ones sort together
     };
+    // whether b continues p in every operand
+    auto continues = [&](const Step& p, const std::vector<Operand>& srcs, const std::vector<Operand>& dsts) {
+        bool joins = srcs.size() == p.srcs->size() && dsts.size() == p.dsts->size();
+        const uint64_t by = p.nelem * es;
+        auto follow = [&](const std::vector<Operand>& a, const std::vector<Operand>& b) {
+            bool same = true;
+            for (size_t k = 0; k < a.size(); ++k)
+                same &= a[k].buf == b[k].buf && a[k].dtype == b[k].dtype && a[k].offset + by == b[k].offset;
+            return same;
+        };
+        return joins && follow(*p.srcs, srcs) && follow(*p.dsts, dsts);
+    };
+    // The chunks of a step mostly follow it in the program: joined as they come, there is less to
+    // hash and sort. Steps that name more than kMaxOperands different sets of buffers (the pairs of a
+    // wide exchange) stay more than that many segments: they are given up as soon as that shows.
     std::vector<Step> steps;
-    std::list<std::vector<Operand>> sorted;  // the order of a step's destinations is free
-    auto by_buf = [](const Operand& a, const Operand& b) { return a.buf < b.buf; };
+    constexpr size_t kSlots = 4 * kMaxOperands;
+    uint64_t seen[kSlots] = {0};  // hashes of the sets, open addressing
+    uint32_t sets = 0;
     for (uint32_t i = d0; i < d1; ++i) {
         const HostDesc& d = all[i];
         if (d.op != f.op || d.redop != f.redop || d.group != f.group || d.fold != f.fold || d.requant != f.requant ||
             !d.deps.empty() || d.nelem == 0 || d.srcs.size() != f.srcs.size() || d.dsts.size() != f.dsts.size())
             return u;
-        for (const auto* list : {&d.srcs, &d.dsts})
-            for (const Operand& o : *list)
-                if (o.dtype != dt) return u;
-        const std::vector<Operand>* dsts = &d.dsts;
-        if (!std::is_sorted(d.dsts.begin(), d.dsts.end(), by_buf)) {
-            sorted.push_back(d.dsts);
-            std::sort(sorted.back().begin(), sorted.back().end(), by_buf);
-            dsts = &sorted.back();
+        if (!steps.empty() && continues(steps.back(), d.srcs, d.dsts)) {
+            steps.back().nelem += d.nelem;
+            continue;
         }
-        uint64_t bufs = 0;
-        for (const auto* list : {&d.srcs, dsts})
-            for (const Operand& o : *list) bufs = (bufs ^ o.buf) * 0x9E3779B97F4A7C15ull + 1;
-        steps.push_back({&d.srcs, dsts, d.nelem, bufs});
+        // (the order of a step's destinations is free, that of its sources is not)
+        uint64_t in = 0, out = 0;
+        for (const Operand& o : d.srcs) {
+            if (o.dtype != dt) return u;
+            in = (in ^ o.buf) * 0x9E3779B97F4A7C15ull + 1;
+        }
+        for (const Operand& o : d.dsts) {
+            if (o.dtype != dt) return u;
+            const uint64_t h = (o.buf + 1) * 0x9E3779B97F4A7C15ull;
+            out += h ^ (h >> 29);
+        }
+        const uint64_t bufs = (in ^ out) | 1;
+        size_t at = (bufs >> 32) % kSlots;
+        while (seen[at] != 0 && seen[at] != bufs) at = (at + 1) % kSlots;
+        if (seen[at] == 0) {
+            seen[at] = bufs;
+            if (++sets > (uint32_t)kMaxOperands) return u;
+        }
+        steps.push_back({&d.srcs, &d.dsts, d.nelem, bufs});
     }
-    // join the steps that continue one another in every operand
+    // all segments are of one length, but for one that may be shorter
+    auto lengths_fit = [](const std::vector<Step>& v) {
+        uint64_t longest = 0;
+        size_t others = 0;
+        for (const Step& d : v) longest = std::max(longest, d.nelem);
+        for (const Step& d : v) others += d.nelem != longest;
+        return others <= 1;
+    };
+    if (sets == steps.size() && !lengths_fit(steps)) return u;  // (no two of these can join)
+    std::list<std::vector<Operand>> sorted;
+    auto by_buf = [](const Operand& a, const Operand& b) { return a.buf < b.buf; };
+    for (Step& d : steps)
+        if (!std::is_sorted(d.dsts->begin(), d.dsts->end(), by_buf)) {
+            sorted.push_back(by_buffer(*d.dsts));
+            d.dsts = &sorted.back();
+        }
+    // join the steps that continue one another elsewhere in the program
     std::stable_sort(steps.begin(), steps.end(), [](const Step& a, const Step& b) {
         return a.bufs != b.bufs ? a.bufs < b.bufs : (*a.dsts)[0].offset < (*b.dsts)[0].offset;
     });
     std::vector<Step> segs;
     for (const Step& d : steps) {
-        bool joins = !segs.empty() && same_bufs(*segs.back().srcs, *d.srcs) && same_bufs(*segs.back().dsts, *d.dsts);
-        if (joins) {
-            const Step& p = segs.back();
-            for (size_t k = 0; k < d.srcs->size(); ++k) joins &= (*d.srcs)[k].offset == (*p.srcs)[k].offset + p.nelem * es;
-            for (size_t k = 0; k < d.dsts->size(); ++k) joins &= (*d.dsts)[k].offset == (*p.dsts)[k].offset + p.nelem * es;
-        }
-        if (joins) segs.back().nelem += d.nelem;
+        if (!segs.empty() && continues(segs.back(), *d.srcs, *d.dsts)) segs.back().nelem += d.nelem;
         else segs.push_back(d);
         if (segs.size() > (size_t)kMaxOperands) return u;
     }
+    if (!lengths_fit(segs)) return u;
     std::stable_sort(segs.begin(), segs.end(), [](const Step& a, const Step& b) {
         const Operand &ad = (*a.dsts)[0], &bd = (*b.dsts)[0], &as = (*a.srcs)[0], &bs = (*b.srcs)[0];
         if (ad.offset != bd.offset) return ad.offset < bd.offset;
@@ -1213,18 +1277,22 @@ UniformPhase find_uniform(const std::vector<HostDesc>& all, uint32_t d0, uint32_
         // copies of one location of every buffer but the source's own (the results of a two-level
         // all-reduce): the list of all of them; a wavefront leaves out the destination that is
         // its source
-        auto with_source = [&](const Step& d) {
-            std::vector<Operand> v = *d.dsts;
-            v.insert(std::upper_bound(v.begin(), v.end(), (*d.srcs)[0], by_buf), (*d.srcs)[0]);
-            return v;
+        const size_t m = dst0.size() + 1;
+        // operand k of a segment's destinations with its source among them
+        auto place = [&](const Step& d) { return std::upper_bound(d.dsts->begin(), d.dsts->end(), (*d.srcs)[0], by_buf) - d.dsts->begin(); };
+        auto with_source = [](const Step& d, size_t at, size_t k) -> const Operand& {
+            return k == at ? (*d.srcs)[0] : (*d.dsts)[k - (k > at)];
         };
-        u.dsts = with_source(s0);
-        u.dst_step = with_source(segs[1])[0].offset - u.dsts[0].offset;
-        for (uint32_t g = 0; g < n; ++g) {
-            const std::vector<Operand> v = with_source(segs[g]);
-            if (!same_bufs(v, u.dsts)) return u;
-            for (size_t k = 0; k < v.size(); ++k)
-                if (v[k].offset != u.dsts[k].offset + g * u.dst_step || (k && v[k].buf == v[k - 1].buf)) return u;
+        for (size_t k = 0; k < m; ++k) u.dsts.push_back(with_source(s0, place(s0), k));
+        for (size_t k = 1; k < m; ++k)
+            if (u.dsts[k].buf == u.dsts[k - 1].buf) return u;
+        u.dst_step = with_source(segs[1], place(segs[1]), 0).offset - u.dsts[0].offset;
+        for (uint32_t g = 1; g < n; ++g) {
+            const size_t at = place(segs[g]);
+            for (size_t k = 0; k < m; ++k) {
+                const Operand& o = with_source(segs[g], at, k);
+                if (o.buf != u.dsts[k].buf || o.offset != u.dsts[k].offset + g * u.dst_step) return u;
+            }
         }
     } else {
         return u;
@@ -1254,26 +1322,39 @@ UniformPhase find_uniform(const std::vector<HostDesc>& all, uint32_t d0, uint32_
 // if the program is not of that form.
 std::vector<CopyEntry> copy_list(const HostProgram& p, uint32_t& ntiles) {
     std::vector<CopyEntry> list;
-    std::unordered_map<uint32_t, size_t> first;  // destination buffer -> its first step
-    struct Piece { size_t first; CopyEntry e; };
-    std::vector<Piece> v;
-    for (size_t i = 0; i < p.descs.size(); ++i) {
-        const HostDesc& d = p.descs[i];
+    // Copies by destination buffer, in the order in which the destinations first come up, then by
+    // source buffer (two counting sorts): those of packed receive ranges are then in their order.
+    constexpr uint32_t kBufs = 2u * kMaxRanks;
+    uint32_t place[kBufs], dst_at[kBufs + 1] = {0}, src_at[kBufs + 1] = {0}, ndst = 0;
+    std::fill_n(place, kBufs, ~0u);
+    for (const HostDesc& d : p.descs) {
         if (d.op != OP_COPY || d.srcs.size() != 1 || d.dsts.size() != 1 || !d.deps.empty() || d.nelem == 0) return list;
-        if (d.srcs[0].buf >= 2u * kMaxRanks || d.dsts[0].buf >= 2u * kMaxRanks) return list;
-        first.emplace(d.dsts[0].buf, i);
-        v.push_back({first[d.dsts[0].buf], {d.srcs[0].offset, d.dsts[0].offset, d.nelem * dtype_size(d.srcs[0].dtype),
-                                            d.srcs[0].buf | d.dsts[0].buf << 16, 0}});
+        if (d.srcs[0].buf >= kBufs || d.dsts[0].buf >= kBufs) return list;
+        uint32_t& k = place[d.dsts[0].buf];
+        if (k == ~0u) k = ndst++;
+        ++dst_at[k + 1];
+        ++src_at[d.srcs[0].buf + 1];
     }
-    std::sort(v.begin(), v.end(), [](const Piece& a, const Piece& b) {
-        return a.first != b.first ? a.first < b.first : a.e.dst_off < b.e.dst_off;
-    });
-    for (const Piece& c : v) {
-        if (!list.empty() && list.back().bufs == c.e.bufs && list.back().src_off + list.back().bytes == c.e.src_off &&
-            list.back().dst_off + list.back().bytes == c.e.dst_off)
-            list.back().bytes += c.e.bytes;
+    for (uint32_t k = 0; k < kBufs; ++k) dst_at[k + 1] += dst_at[k], src_at[k + 1] += src_at[k];
+    std::vector<uint32_t> by_src(p.descs.size());
+    for (size_t i = 0; i < p.descs.size(); ++i) by_src[src_at[p.descs[i].srcs[0].buf]++] = (uint32_t)i;
+    std::vector<CopyEntry> v(p.descs.size());
+    for (uint32_t i : by_src) {
+        const Operand &s = p.descs[i].srcs[0], &t = p.descs[i].dsts[0];
+        v[dst_at[place[t.buf]]++] = {s.offset, t.offset, p.descs[i].nelem * dtype_size(s.dtype), s.buf | t.buf << 16, 0};
+    }
+    auto by_offset = [](const CopyEntry& a, const CopyEntry& b) { return a.dst_off < b.dst_off; };
+    for (uint32_t k = 0; k < ndst; ++k) {  // (dst_at[k] is where destination k ends now)
+        const auto from = v.begin() + (k ? dst_at[k - 1] : 0u), to = v.begin() + dst_at[k];
+        if (!std::is_sorted(from, to, by_offset)) std::sort(from, to, by_offset);
+    }
+    list.reserve(v.size());
+    for (const CopyEntry& e : v) {
+        if (!list.empty() && list.back().bufs == e.bufs && list.back().src_off + list.back().bytes == e.src_off &&
+            list.back().dst_off + list.back().bytes == e.dst_off)
+            list.back().bytes += e.bytes;
         else
-            list.push_back(c.e);
+            list.push_back(e);
     }
     uint64_t t = 0;
     for (CopyEntry& e : list) {
@@ -1292,23 +1373,24 @@ std::vector<CopyEntry> copy_list(const HostProgram& p, uint32_t& ntiles) {
 bool finalize(HostProgram& p, uint32_t tile_bytes, std::string& err) {
     // compact
     std::vector<int64_t> remap(p.descs.size(), -1);
-    std::vector<HostDesc> live;
+    size_t live = 0;
     for (size_t i = 0; i < p.descs.size(); ++i) {
         if (!p.descs[i].alive) continue;
-        remap[i] = (int64_t)live.size();
-        live.push_back(std::move(p.descs[i]));
+        remap[i] = (int64_t)live;
+        if (live != i) p.descs[live] = std::move(p.descs[i]);
+        ++live;
     }
-    for (size_t i = 0; i < live.size(); ++i) {
-        for (Dep& d : live[i].deps) {
+    p.descs.resize(live);
+    for (size_t i = 0; i < live; ++i) {
+        for (Dep& d : p.descs[i].deps) {
             if (remap[d.desc] < 0) {
                 err = "dependency on a removed step";
                 return false;
             }
             d.desc = (uint32_t)remap[d.desc];
         }
-        dedupe_deps(live[i], (uint32_t)i);
+        dedupe_deps(p.descs[i], (uint32_t)i);
     }
-    p.descs = std::move(live);
 
     // Phases. A step's level is 0 without dependencies, else one more than the highest level it
     // waits for. Run level by level, one launch each, every dependency is met by the launch
@@ -1401,7 +1483,10 @@ bool finalize(HostProgram& p, uint32_t tile_bytes, std::string& err) {
     std::vector<Desc> out(nd);
     std::vector<Operand> ops;
     std::vector<Dep> deps;
-    std::vector<uint32_t> tile_owner;
+    size_t nops = 0, nedges = 0;
+    for (const HostDesc& h : p.descs) nops += h.srcs.size() + h.dsts.size(), nedges += h.deps.size();
+    ops.reserve(nops);
+    deps.reserve(nedges);
     uint64_t ntiles = 0;
     p.bytes_read = p.bytes_written = 0;
     p.max_srcs = 0;
@@ -1462,7 +1547,6 @@ bool finalize(HostProgram& p, uint32_t tile_bytes, std::string& err) {
         p.max_srcs = std::max<uint32_t>(p.max_srcs, d.nsrc);
         for (const Operand& o : h.srcs) p.bytes_read += h.nelem * dtype_size(o.dtype);
         for (const Operand& o : h.dsts) p.bytes_written += h.nelem * dtype_size(o.dtype);
-        for (uint64_t t = 0; t < nt; ++t) tile_owner.push_back(i);
     }
     p.ntiles = (uint32_t)ntiles;
     p.nstate = has_deps ? (uint32_t)(kStateDescBase + nd + ntiles) : kStateDescBase;
@@ -1542,7 +1626,7 @@ bool finalize(HostProgram& p, uint32_t tile_bytes, std::string& err) {
     hdr.off_operand = align16(hdr.off_desc + (uint64_t)nd * sizeof(Desc));
     hdr.off_dep = align16(hdr.off_operand + ops.size() * sizeof(Operand));
     hdr.off_tile_desc = align16(hdr.off_dep + deps.size() * sizeof(Dep));
-    hdr.off_aux = align16(hdr.off_tile_desc + tile_owner.size() * sizeof(uint32_t));
+    hdr.off_aux = align16(hdr.off_tile_desc + (uint64_t)p.ntiles * sizeof(uint32_t));
     hdr.naux = (uint32_t)p.aux.size();
     hdr.nphase = nphase;
     hdr.off_phase = align16(hdr.off_aux + p.aux.size() * sizeof(DynA2A));
@@ -1564,8 +1648,8 @@ bool finalize(HostProgram& p, uint32_t tile_bytes, std::string& err) {
     if (nd) std::memcpy(p.image.data() + hdr.off_desc, out.data(), (size_t)nd * sizeof(Desc));
     if (!ops.empty()) std::memcpy(p.image.data() + hdr.off_operand, ops.data(), ops.size() * sizeof(Operand));
     if (!deps.empty()) std::memcpy(p.image.data() + hdr.off_dep, deps.data(), deps.size() * sizeof(Dep));
-    if (!tile_owner.empty())
-        std::memcpy(p.image.data() + hdr.off_tile_desc, tile_owner.data(), tile_owner.size() * sizeof(uint32_t));
+    uint32_t* owner = (uint32_t*)(p.image.data() + hdr.off_tile_desc);  // (the image is allocated at any type's alignment)
+    for (uint32_t i = 0; i < nd; ++i) owner = std::fill_n(owner, out[i].ntiles, i);
     if (!p.aux.empty()) std::memcpy(p.image.data() + hdr.off_aux, p.aux.data(), p.aux.size() * sizeof(DynA2A));
     if (!list.empty()) {
         std::memcpy(p.image.data() + off_list, ends.data(), ends.size() * sizeof(uint32_t));
