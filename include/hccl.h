@@ -33,6 +33,10 @@
  * CUs of the device (a triggered packet of this process not yet released, a resident executor),
  * such programs take their tiles by atomic ticket, which completes on whatever part of the
  * grid is resident. Kernels of other processes that never finish are not known to the library.
+ * An hccl_alltoallv_dynamic of more than 8 ranks that is a packet of its own plans in workgroups of
+ * 16 wavefronts with 69 KiB of LDS; while such a waiting kernel is there, and in a captured graph
+ * (which may be replayed beside one), it runs in the executor's workgroups of 4 wavefronts
+ * instead. Enqueued before a kernel that waits for it, it needs a CU with that much room left.
  * While a triggered packet waits, the library also makes no call that could wait for every
  * stream of the device: programs are uploaded on a stream of the communicator that waits for
  * no other, and memory it would free (evicted programs, outgrown scratch) is kept until

@@ -570,14 +570,15 @@ constexpr uint64_t kDynamicTileBytes = 4096;
 // A program that is one AllToAllvDynamic, of the default tiles and of capacities whose row numbers
 // fit 32 bits, has kernels of its own (for above 8 ranks a workgroup plans with 16 wavefronts, so a
 // smaller configured bound keeps the executor's).
-bool lone_dynamic(const hcclComm* c, const std::vector<CollectiveSpec>& specs) {
+bool lone_dynamic(const hcclComm* c, const std::vector<CollectiveSpec>& specs, bool capturing) {
     if (specs.size() != 1 || specs[0].coll != COLL_ALLTOALLV_DYNAMIC || specs[0].tile_bytes != 0) return false;
     const CollectiveSpec& s = specs[0];
     const uint64_t cap = std::max(s.send_cap, s.recv_cap), P = (uint64_t)s.P;
     if (cap >= (1ull << 31) / P || cap * s.row_elems * dtype_size((uint32_t)s.dtype) / kDynamicTileBytes + P >= (1ull << 31) / P) return false;
     // a kernel that waits for something still to come may leave a CU room for four wavefronts and
-    // not for sixteen, and what it waits for may be this call
-    if (s.P > 8 && (trigger_pending(c->device) || resident_running(c->device))) return false;
+    // not for sixteen, and what it waits for may be this call; a graph is replayed when such a
+    // kernel may be there, whatever is there while it is captured
+    if (s.P > 8 && (capturing || trigger_pending(c->device) || resident_running(c->device))) return false;
     return c->cfg.max_workers <= 0 || (uint32_t)c->cfg.max_workers >= dynamic_waves_per_block((uint32_t)s.P);
 }
 
@@ -795,7 +796,7 @@ hcclResult_t run_packet(hcclComm* c, const std::vector<Call>& calls) {
     int kind = 0;
     info.tickets = a.dynamic;
     const bool packed = inline_eligible(c, triggered);
-    const bool lone = packed && lone_dynamic(c, specs);
+    const bool lone = packed && lone_dynamic(c, specs, capturing);
     info.inline_launch = lone || (packed && all_uniform(dp->prog)) ? 1 : 0;
 
     // a program's counters serve one launch at a time, and the communicator's scratch one

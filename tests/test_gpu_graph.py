@@ -131,6 +131,43 @@ def test_captured_dynamic_exchange_follows_device_counts():
                 assert np.array_equal(to_host(recv[d], "int32"), want[d]), f"replay {k} destination {d}"
 
 
+@pytest.mark.parametrize("P", [9, 64])
+def test_captured_dynamic_exchange_of_many_ranks_keeps_small_workgroups(P):
+    """A graph may be replayed beside a kernel that holds part of every CU while it waits for
+    something the graph does: the exchange is captured in the executor's workgroups of 4
+    wavefronts, not in the 16 of the eager launch, and gives the same results."""
+    R, S = 24, 40
+    cap = P * S
+    rng = np.random.default_rng(12 + P)
+    x = inputs(P, S * R, "bf16", 81)
+    send = [to_device(x[s], "bf16") for s in range(P)]
+    recv = [torch.empty(cap * R, dtype=torch.bfloat16, device="cuda:0") for _ in range(P)]
+    d_counts = torch.zeros(P * P, dtype=torch.int64, device="cuda:0")
+    side = torch.cuda.Stream()
+    print(f"graph alltoallv_dynamic P={P} rows={R}", flush=True)
+    packed = []
+    with H.Comm(P, device=0) as c:
+        def step():
+            c.alltoallv_dynamic(send, d_counts, recv, R, stream=side)
+            packed.append(c.last_program()["inline_launch"])
+
+        g = capture(step, side)
+        assert packed == [1, 0]     # eager, captured
+        for k in range(REPLAYS):
+            counts = rng.multinomial(S, rng.dirichlet(np.full(P, 0.5)), size=P)
+            d_counts.copy_(torch.from_numpy(counts.reshape(-1).astype(np.int64)).to("cuda:0"))
+            for t in recv:
+                t.fill_(-1)
+            torch.cuda.synchronize()
+            g.replay()
+            torch.cuda.synchronize()
+            assert c.async_error() == 0
+            want = [to_host(torch.full((cap * R,), -1, dtype=torch.bfloat16), "bf16") for _ in range(P)]
+            assert oracle.alltoallv_dynamic([x[s] for s in range(P)], counts, want, R, S, cap)[0]
+            for d in range(P):
+                assert np.array_equal(to_host(recv[d], "bf16"), want[d]), f"replay {k} destination {d}"
+
+
 def test_first_call_under_capture_is_refused_and_enqueues_nothing():
     P, N = 4, 4096
     send = [torch.ones(N, dtype=torch.float32, device="cuda:0") for _ in range(P)]
