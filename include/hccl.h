@@ -210,9 +210,12 @@ hcclResult_t hccl_allreduce(hcclComm_t comm, const void* const* sendbufs, void* 
  * that the library holds on every device it runs on until the process ends; the call makes no
  * hipMalloc, hipFree or other device allocation (its program is compiled, and cached, in host
  * memory). On `stream` it copies the program into the workspace, clears the counters of a
- * program that waits on the device with a fill kernel, and launches the executor (a program
- * that travels in its launch packets does not touch the workspace). The communicator must have a device (its error record, allocated
- * by hccl_comm_create, is used); the inputs and outputs are the caller's as usual.
+ * program that waits on the device with a fill kernel, and launches the executor. A program that
+ * travels in its launch packets (hcclProgramInfo_t.inline_launch) copies and clears nothing; its
+ * partials, if it has any (scratch_bytes above 0: unfused schedules), still live in the workspace,
+ * and only one without them leaves the workspace alone. The communicator must have a device (its
+ * error record, allocated by hccl_comm_create, is used); the inputs and outputs are the caller's
+ * as usual.
  * Every call on one device shares that workspace and finds it as the last call left it: calls
  * whose work can overlap in time on one GPU (other streams, other communicators) race, and the
  * caller must order them. A call that needs more than the workspace holds (image + counters +

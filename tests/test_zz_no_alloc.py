@@ -30,6 +30,8 @@ CASES = [
     ("recursive halving unfused bf16", 8, "bf16", dict(algo="rhd", order="halving", fuse=0, phases="one"), 100_000,
      4_097, {"order": "halving"}),
     ("ring fused fp32", 8, "fp32", dict(algo="ring", chunk_bytes=65536), 1 << 20, 12_345, {}),
+    # in launch packets, phase by phase, their partials in the workspace all the same
+    ("ring unfused fp32, in launch packets", 8, "fp32", dict(algo="ring", fuse=0, chunk_bytes=16384), 300_001, 70_003, {}),
     ("one-step direct fp32", 8, "fp32", dict(algo="direct"), 1 << 14, 1000, {}),
 ]
 
@@ -64,6 +66,8 @@ def test_noalloc_matches_allreduce_on_two_calls_second_smaller(case):
             if cfg.get("fuse") == 0 and P > 2:
                 assert info["scratch_bytes"] > 0, info                            # partials used
                 assert (info["num_deps"] > 0) == (cfg.get("phases") == "one"), info  # counters used
+            if "in launch packets" in label:
+                assert info["inline_launch"] == 1, info
             if cfg.get("phases") == "levels" or (cfg.get("fuse") == 0 and "phases" not in cfg):
                 assert info["num_phases"] > 1, info
             want = _want(x, dt, order)
