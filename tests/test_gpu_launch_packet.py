@@ -9,8 +9,8 @@ import oracle
 import paper_2608_00358_amd as H
 from gpu_helpers import Guarded, first_mismatch, same_bits, to_device
 from test_gpu_dynamic import random_counts, run_dynamic
-from test_gpu_orders import run_ar, run_rs
-from test_gpu_parity import run_allgather, run_allreduce, run_reduce_scatter
+from test_gpu_orders import lib_shard, run_ar, run_rs
+from test_gpu_parity import inputs, run_allgather, run_allreduce, run_reduce_scatter
 
 pytestmark = pytest.mark.gpu
 
@@ -83,6 +83,51 @@ def test_every_offset_from_a_boundary(dt, order, op):
                 got = outs[r].result()[b:]
                 assert same_bits(got, want[r], dt), f"rank {r}: {first_mismatch(got, want[r])}"
                 assert outs[r].guards_intact()
+
+
+# fold, ranks, element type, operator, configuration
+IN_PLACE = [
+    ("list", 2, "bf16", "sum", {}), ("list", 3, "fp32", "sum", {}), ("list", 8, "fp16", "sum", {}),
+    ("list", 9, "bf16", "sum", {}), ("list", 17, "int32", "sum", {}), ("list", 64, "fp32", "sum", {}),
+    ("ring", 8, "bf16", "sum", {}), ("ring", 16, "fp32", "sum", {}),
+    ("tree", 4, "fp16", "sum", {}), ("tree", 16, "bf16", "sum", {}), ("tree", 32, "fp32", "sum", {}),
+    ("tree", 8, "bf16", "sum", {"requantize": 1}), ("list", 12, "fp16", "sum", {"requantize": 1}),
+    ("group", 6, "bf16", "sum", {"algo": "two_level", "group_size": 3}),
+    ("group", 16, "fp32", "sum", {"algo": "two_level", "group_size": 8}),
+    ("group", 16, "bf16", "sum", {"algo": "two_level", "group_size": 8, "phases": "levels"}),
+    ("list", 8, "bf16", "max", {}), ("list", 9, "fp32", "min", {}), ("ring", 4, "int32", "max", {}),
+]
+
+
+@pytest.mark.parametrize("fold,P,dt,op,cfg", IN_PLACE)
+def test_in_place(fold, P, dt, op, cfg):
+    """Results over their own inputs: in the last step of a tile a lane reads again what its neighbour
+    is about to overwrite. Views that begin on a boundary, and 1 or 3 elements after one."""
+    order = {"ring": "ring", "tree": "halving"}.get(fold, "ascending")
+    # (sub-shards of one length: the two-level schedule's phases are then uniform)
+    sizes = [64 * P, 64 * P * 3, 64 * P * 17] if fold == "group" else SIZES
+    with H.Comm(P, device=0, order=order, **cfg) as c:
+        for n in sizes:
+            x = inputs(P, n, dt, seed=P * 13 + n)
+            if op != "sum":
+                want = oracle.allreduce(x, dt, op=op)
+            elif fold == "group":
+                want = oracle.allreduce(x, dt, group=cfg["group_size"])
+            else:
+                want = oracle.allreduce_ordered(x, dt, order=order, shard=lib_shard(n, P), requant=bool(cfg.get("requantize")))
+            for at in (0, 1, 3):
+                print(f"in place {fold} P={P} {dt} {op} n={n} offset {at} {cfg}", flush=True)
+                bufs = [Guarded(n + at, dt, fill=np.concatenate([np.zeros(at, x.dtype), x[r]])) for r in range(P)]
+                views = [b.view[at:] for b in bufs]
+                H.hccl_allreduce(c.handle, views, views, n, dt, op)
+                torch.cuda.synchronize()
+                assert c.async_error() == 0
+                assert c.last_program()["inline_launch"] == 1
+                for r in range(P):
+                    got = bufs[r].result()
+                    assert not got[:at].any()
+                    assert same_bits(got[at:], want[r], dt), f"rank {r}: {first_mismatch(got[at:], want[r])}"
+                    assert bufs[r].guards_intact()
 
 
 def to_device_bits(v, dt):
