@@ -3,8 +3,8 @@
 Packed FP32 arithmetic (and the packed 32-bit move of the same instruction group) is disabled
 for all device code, yet the compiler still emits the packed move for some vector shuffles, so
 the build disassembles every code object it makes and rejects one that holds such an
-instruction. These tests check that the built executor passes and that a kernel which does
-hold one is rejected (it is only compiled, never run).
+instruction. These tests check that every file of the built executor passes and that a kernel
+which does hold one is rejected (it is only compiled, never run).
 """
 import os
 import subprocess
@@ -34,8 +34,9 @@ def _hipcc():
         pytest.skip("hipcc is not available")
 
 
-def test_built_executor_holds_no_packed_fp32():
-    obj = os.path.join(_build.OBJDIR, "executor.hip.o")
+@pytest.mark.parametrize("src", _build.EXECUTOR_SOURCES)
+def test_built_executor_holds_no_packed_fp32(src):
+    obj = os.path.join(_build.OBJDIR, src + ".o")
     if not os.path.exists(obj):
         pytest.skip("the executor is not built")
     _build.check_device_code(obj)
@@ -49,3 +50,10 @@ def test_check_rejects_a_kernel_with_a_packed_move(tmp_path):
     assert res.returncode == 0, res.stderr
     with pytest.raises(RuntimeError, match="v_pk_mov_b32"):
         _build.check_device_code(str(obj))
+
+
+def test_every_device_source_is_checked():
+    """Sources with kernels are the executor's, all of which the build and the test above check."""
+    csrc = _build.CSRC
+    kernels = [f for f in os.listdir(csrc) if f.endswith((".hip", ".cpp")) and "hipLaunchKernelGGL" in open(os.path.join(csrc, f)).read()]
+    assert sorted(kernels) == sorted(_build.EXECUTOR_SOURCES)
