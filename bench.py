@@ -1080,9 +1080,19 @@ def cpu_baseline(w, budget_s=10.0, par_budget_s=5.0):
 
 
 # ------------------------------------------------------------------------ roofline
+def library_digest(csrc: str = os.path.join(ROOT, "paper_2608_00358_amd", "csrc")) -> str:
+    """Digest of the library's sources: the kernels, and the host code that chooses among them, cuts
+    their tiles and sizes their grids."""
+    digest = hashlib.sha256()
+    for src in sorted(glob.glob(os.path.join(csrc, "*"))):
+        with open(src, "rb") as f:
+            digest.update(f.read())
+    return digest.hexdigest()[:16]
+
+
 def traffic_record(kernel: str):
     """HBM bytes per launch from committed rocprofv3 counter runs, if they were taken on
-    the current executor source (otherwise null)."""
+    the current sources of the library (otherwise null)."""
     path = os.path.join(ROOT, "profiles", "traffic.json")
     if not os.path.exists(path):
         return None
@@ -1090,13 +1100,8 @@ def traffic_record(kernel: str):
         rec = json.load(open(path))
     except ValueError:
         return None
-    digest = hashlib.sha256()
-    for src in sorted(glob.glob(os.path.join(ROOT, "paper_2608_00358_amd", "csrc", "executor*"))):
-        with open(src, "rb") as f:
-            digest.update(f.read())
-    digest = digest.hexdigest()[:16]
     entry = rec.get(kernel)
-    if not entry or entry.get("executor_sha256_16") != digest:
+    if not entry or entry.get("library_sha256_16") != library_digest():
         return None
     return entry.get("bytes_per_launch")
 
