@@ -533,10 +533,22 @@ bool inline_eligible(const hcclComm* c, bool triggered) {
     return c->inline_single_step && c->dispatch_mode != 2 && !triggered && !c->cfg.trace;
 }
 
+// Whether every operand of every tile of a uniform phase is 16-byte aligned (tiles are whole vectors,
+// so the first element of every segment decides).
+bool all_aligned(const UniformPhase& u, char* const* bufs) {
+    uint64_t any = u.nseg > 1 ? u.src_step | u.dst_step : 0u;
+    for (const Operand& o : u.srcs) any |= (uint64_t)(uintptr_t)bufs[o.buf] + o.offset;
+    for (const Operand& o : u.dsts) any |= (uint64_t)(uintptr_t)bufs[o.buf] + o.offset;
+    return any % 16 == 0;
+}
+
+// Whether a phase travels in its launch packet when it runs on these buffers.
+bool takes_packet(const UniformPhase& u, char* const* bufs) { return u.ok && !(u.long_run && all_aligned(u, bufs)); }
+
 // Whether nothing of a program needs its image.
-bool all_uniform(const HostProgram& prog) {
+bool all_uniform(const HostProgram& prog, char* const* bufs) {
     for (const UniformPhase& u : prog.uniform)
-        if (!u.ok) return false;
+        if (!takes_packet(u, bufs)) return false;
     return !prog.uniform.empty();
 }
 
@@ -628,12 +640,9 @@ hipError_t launch_uniform_phase(const hcclComm* c, const UniformPhase& u, char* 
     a.group = u.group;
     a.flags = u.flags;
     a.per_wave = u.per_wave;
-    // tiles are whole vectors, so the first element of every segment decides the alignment
-    uint64_t any = 0;
-    for (size_t i = 0; i < u.srcs.size(); ++i) any |= a.src[i] = (uint64_t)(uintptr_t)bufs[u.srcs[i].buf] + u.srcs[i].offset;
-    for (size_t i = 0; i < u.dsts.size(); ++i) any |= a.dst[i] = (uint64_t)(uintptr_t)bufs[u.dsts[i].buf] + u.dsts[i].offset;
-    if (u.nseg > 1) any |= u.src_step | u.dst_step;
-    if (any % 16 == 0) a.flags |= UF_ALIGNED;
+    for (size_t i = 0; i < u.srcs.size(); ++i) a.src[i] = (uint64_t)(uintptr_t)bufs[u.srcs[i].buf] + u.srcs[i].offset;
+    for (size_t i = 0; i < u.dsts.size(); ++i) a.dst[i] = (uint64_t)(uintptr_t)bufs[u.dsts[i].buf] + u.dsts[i].offset;
+    if (all_aligned(u, bufs)) a.flags |= UF_ALIGNED;
     const uint32_t wpb = (uint32_t)executor_waves_per_block();
     workers = std::min<uint32_t>(a.ntiles, kMaxGridWorkers);
     if (c->cfg.max_workers > 0) workers = std::min<uint32_t>(workers, (uint32_t)c->cfg.max_workers);
@@ -797,7 +806,7 @@ hcclResult_t run_packet(hcclComm* c, const std::vector<Call>& calls) {
     info.tickets = a.dynamic;
     const bool packed = inline_eligible(c, triggered);
     const bool lone = packed && lone_dynamic(c, specs, capturing);
-    info.inline_launch = lone || (packed && all_uniform(dp->prog)) ? 1 : 0;
+    info.inline_launch = lone || (packed && all_uniform(dp->prog, a.bufs)) ? 1 : 0;
 
     // a program's counters serve one launch at a time, and the communicator's scratch one
     // program at a time: order such launches across streams. A captured launch is left out of
@@ -831,7 +840,7 @@ hcclResult_t run_packet(hcclComm* c, const std::vector<Call>& calls) {
             e = launch_list(c, dp->prog, a, s, a.nworkers);
             if (e != hipSuccess) return hip_fail(e, "copy list launch");
             hlog(c, 3, "launched the copy list: %u entries, %u wavefronts", dp->prog.list_entries, a.nworkers);
-        } else if (packed && dp->prog.uniform[q].ok) {
+        } else if (packed && takes_packet(dp->prog.uniform[q], a.bufs)) {
             e = launch_uniform_phase(c, dp->prog.uniform[q], a.bufs, s, a.nworkers);
             if (e != hipSuccess) return hip_fail(e, "uniform launch");
             hlog(c, 3, "launched phase %u of %u from the launch packet: %u wavefronts", q + 1, nph, a.nworkers);
@@ -1140,7 +1149,7 @@ hcclResult_t hccl_allreduce_noalloc(hcclComm_t comm, const void* const* sendbufs
     comm->last.workers = a.nworkers;
     comm->last.tickets = a.dynamic;
     hipError_t e;
-    if (inline_eligible(comm, false) && all_uniform(*hp)) {
+    if (inline_eligible(comm, false) && all_uniform(*hp, a.bufs)) {
         comm->last.inline_launch = 1;
         for (uint32_t q = 0; q < hp->nphase(); ++q) {
             uint32_t workers = 0;

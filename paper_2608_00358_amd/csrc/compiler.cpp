@@ -1061,9 +1061,14 @@ constexpr uint64_t kUniformFewWaves = 16384;
 // 4 x 4 MiB: ordinary stores 7.8, non-temporal 6.9), unless a later phase of the program reads them.
 constexpr uint64_t kUniformCachedBytes = 8ull << 20;
 
-// Copies of this many bytes to this many destinations stay on the executor's kernel, whose 32 KiB
-// tiles write runs of 8 KiB to each destination in turn: the copy phase of the two-level all-reduce of
-// 64 ranks, executor / uniform: 32 MiB per rank 719 / 750 us for the call, 8 MiB 183 / 176.
+// Copies of this many bytes to this many destinations stay on the executor's kernel where every
+// operand is 16-byte aligned: its 32 KiB tiles write runs of 8 KiB to each destination in turn.
+// Executor / uniform: two-level all-reduce of 64 ranks, whose second phase is such a copy, 8 MiB per
+// rank 182 / 175 us for the call, 16 MiB 357 / 365, 32 MiB 720 / 758, of 32 ranks x 32 MiB 362 / 372;
+// all-gather of 64 blocks of 128 KiB 101 / 89, of 256 KiB 198 / 194, 512 KiB 389 / 395, 1 MiB
+// 747 / 833; of 32 blocks of 512 KiB 98 / 97, 1 MiB 199 / 192, 2 MiB 389 / 391. Other alignments
+// take the executor to single elements: 32 blocks of 300 001 fp32 378 / 238, 64 of them
+// 1350 / 895, 64 of 262 144 fp32 one element off a boundary 1055 / 805.
 constexpr uint64_t kLongRunDsts = 32;
 constexpr uint64_t kLongRunBytes = 16ull << 20;
 // So does one large copy by itself (one rank, 1 GiB: executor 355 us, uniform 370, as a list 360).
@@ -1312,8 +1317,8 @@ UniformPhase find_uniform(const std::vector<HostDesc>& all, uint32_t d0, uint32_
     u.per_wave = 1;
     if (tile) u.tile_elems = tile;
     else uniform_tile(u, total);
-    u.ok = u.ntiles() < (1ull << 31) && !(f.op == OP_COPY && u.ndst() >= kLongRunDsts && total * es >= kLongRunBytes) &&
-           !one_long_copy(f.op, u.nseg, u.ndst(), total * es);
+    u.long_run = f.op == OP_COPY && u.ndst() >= kLongRunDsts && total * es >= kLongRunBytes;
+    u.ok = u.ntiles() < (1ull << 31) && !one_long_copy(f.op, u.nseg, u.ndst(), total * es);
     return u;
 }
 

@@ -84,6 +84,7 @@ struct HostDesc {
 // addresses, by which buffer it reads or writes, or by a rotation of its source list.
 struct UniformPhase {
     bool ok = false;
+    bool long_run = false;                // the executor's where every operand is 16-byte aligned
     UniformKernel kernel{};
     uint32_t group = 0;
     uint32_t nseg = 0;

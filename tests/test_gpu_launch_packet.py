@@ -62,6 +62,25 @@ def test_allgather(dt, P):
         run_allgather(P, m, dt)
 
 
+@pytest.mark.parametrize("n,offset,packed", [(262144, 0, 0), (262144, 1, 1), (262147, 0, 1), (200000, 0, 1)])
+def test_large_allgather_of_32_ranks(n, offset, packed):
+    """16 MiB and more to 32 destinations: the executor's long runs for aligned blocks alone."""
+    P = 32
+    print(f"allgather P={P} n={n} offset {offset}", flush=True)
+    rng = np.random.default_rng(n)
+    send = [to_device(np.concatenate([np.zeros(offset, np.uint16), rng.integers(0, 1 << 15, n).astype(np.uint16)]), "bf16")[offset:]
+            for _ in range(P)]
+    whole = torch.zeros((P, P * n + 2 * 64), dtype=torch.bfloat16, device="cuda:0")
+    with H.Comm(P, device=0) as c:
+        H.hccl_allgather(c.handle, send, [w[64 + offset:64 + offset + P * n] for w in whole], n, "bf16")
+        torch.cuda.synchronize()
+        assert c.last_program()["inline_launch"] == packed
+    want = torch.zeros_like(whole[0]).view(torch.int16)
+    want[64 + offset:64 + offset + P * n] = torch.cat(send).view(torch.int16)
+    for w in whole:
+        assert torch.equal(w.view(torch.int16), want)
+
+
 @pytest.mark.parametrize("dt,order", [("bf16", "halving"), ("fp16", "ring"), ("fp32", "halving")])
 @pytest.mark.parametrize("op", ["sum", "max"])
 def test_every_offset_from_a_boundary(dt, order, op):
