@@ -634,15 +634,15 @@ hipError_t launch_uniform_phase(const hcclComm* c, const UniformPhase& u, char* 
     a.nseg = u.nseg;
     a.tile_elems = u.tile_elems;
     a.tiles_per_seg = (uint32_t)u.tiles_per_seg();
-    a.ntiles = (uint32_t)u.ntiles();
+    const bool aligned = all_aligned(u, bufs);
+    a.per_wave = aligned ? u.aligned_per_wave : u.per_wave;
+    a.ntiles = (uint32_t)u.ntiles(a.per_wave);
     a.nsrc = u.nsrc();
     a.ndst = u.ndst();
     a.group = u.group;
-    a.flags = u.flags;
-    a.per_wave = u.per_wave;
+    a.flags = u.flags | (aligned ? (uint32_t)UF_ALIGNED : 0u);
     for (size_t i = 0; i < u.srcs.size(); ++i) a.src[i] = (uint64_t)(uintptr_t)bufs[u.srcs[i].buf] + u.srcs[i].offset;
     for (size_t i = 0; i < u.dsts.size(); ++i) a.dst[i] = (uint64_t)(uintptr_t)bufs[u.dsts[i].buf] + u.dsts[i].offset;
-    if (all_aligned(u, bufs)) a.flags |= UF_ALIGNED;
     const uint32_t wpb = (uint32_t)executor_waves_per_block();
     workers = std::min<uint32_t>(a.ntiles, kMaxGridWorkers);
     if (c->cfg.max_workers > 0) workers = std::min<uint32_t>(workers, (uint32_t)c->cfg.max_workers);

@@ -1052,8 +1052,15 @@ constexpr uint64_t kUniformStepBytes = kWaveSize * 16;
 // others left to its neighbours, while that makes fewer than this many wavefronts. One / four /
 // all: all-gather of 8 x 8 MiB 96.7 / 96.5 / 86.4 us; of 8 x 1.2 MB 15.9 / 15.5 / 16.8; of
 // 32 x 13.8 KB 6.3 / 5.5 / 17.3; of 64 x 9 KB 8.9 / 7.9 / 24.0.
+// Segments whose length is a power of two, from this many tiles on, are the exception where they are
+// aligned: neighbours that write the same place of different buffers then meet in the same
+// memory channels. Four / all: all-gather of 32 x 128 KiB 29.3 / 21.6 us (executor 27.0), of 16 x
+// 256 KiB 14.2 / 11.3, of 8 x 1 MiB 12.2 / 11.3; but of 32 x 131 200 bytes 28.5 / 28.9, of
+// 64 x 131 200 99.7 / 110.7, with fewer tiles of 16 x 128 KiB 7.5 / 9.2, to fewer of 5 x 1 MiB
+// 5.8 / 6.2.
 constexpr uint32_t kUniformFewDsts = 4;
 constexpr uint64_t kUniformFewWaves = 16384;
+constexpr uint64_t kUniformWholeTiles = 1024;
 // A reduction that moves no more than this finds its inputs in the caches, where the producer left
 // them: ordinary loads (all-reduce of 8 x 64 KiB 6.0 -> 4.9 us back to back); beyond it the
 // non-temporal ones are as good or better (of 8 x 2 MiB 7.6 / 6.8, of 16 x 8 MiB 26.4 / 23.9, the
@@ -1089,6 +1096,10 @@ void uniform_tile(UniformPhase& u, uint64_t elems) {
         const bool split = (elems * es + bytes - 1) / bytes * few < kUniformFewWaves;
         u.per_wave = split ? std::min(kUniformFewDsts, u.ndst()) : u.ndst();
         sets = split ? few : 1;
+        const uint64_t segment = u.seg_elems * es;
+        const bool resonant = (segment & (segment - 1)) == 0 && u.ndst() >= 2 * kUniformFewDsts &&
+                              elems * es / bytes >= kUniformWholeTiles;
+        u.aligned_per_wave = resonant ? u.ndst() : u.per_wave;
     }
     while (bytes > kUniformStepBytes && elems * es / bytes * sets < want) bytes /= 2;
     u.tile_elems = (uint32_t)(bytes / es);
@@ -1314,11 +1325,11 @@ UniformPhase find_uniform(const std::vector<HostDesc>& all, uint32_t d0, uint32_
     if (f.op == OP_REDUCE && (f.redop != RO_SUM || dt == DT_INT32 || dt == DT_FP32)) u.kernel.requant = false;
     if (f.op == OP_REDUCE && reread) u.kernel.mem = MEM_STORE;
     else if (f.op == OP_REDUCE && total * es * (u.nsrc() + u.ndst()) <= kUniformCachedBytes) u.kernel.mem = MEM_LOAD;
-    u.per_wave = 1;
+    u.per_wave = u.aligned_per_wave = 1;
     if (tile) u.tile_elems = tile;
     else uniform_tile(u, total);
     u.long_run = f.op == OP_COPY && u.ndst() >= kLongRunDsts && total * es >= kLongRunBytes;
-    u.ok = u.ntiles() < (1ull << 31) && !one_long_copy(f.op, u.nseg, u.ndst(), total * es);
+    u.ok = u.ntiles(u.per_wave) < (1ull << 31) && !one_long_copy(f.op, u.nseg, u.ndst(), total * es);
     return u;
 }
 

@@ -62,10 +62,12 @@ def test_allgather(dt, P):
         run_allgather(P, m, dt)
 
 
-@pytest.mark.parametrize("n,offset,packed", [(262144, 0, 0), (262144, 1, 1), (262147, 0, 1), (200000, 0, 1)])
-def test_large_allgather_of_32_ranks(n, offset, packed):
-    """16 MiB and more to 32 destinations: the executor's long runs for aligned blocks alone."""
-    P = 32
+@pytest.mark.parametrize("P,n,offset,packed", [(32, 262144, 0, 0), (32, 262144, 1, 1), (32, 262147, 0, 1), (32, 200000, 0, 1),
+                                               (16, 131072, 0, 1), (16, 131072, 1, 1), (9, 262144, 0, 1), (7, 524288, 0, 1)])
+def test_large_allgather(P, n, offset, packed):
+    """16 MiB and more to 32 destinations: the executor's long runs for aligned blocks alone. Blocks of
+    a power of two bytes, in 1024 tiles and more: a wavefront writes all destinations where they
+    are aligned and there are 8 or more."""
     print(f"allgather P={P} n={n} offset {offset}", flush=True)
     rng = np.random.default_rng(n)
     send = [to_device(np.concatenate([np.zeros(offset, np.uint16), rng.integers(0, 1 << 15, n).astype(np.uint16)]), "bf16")[offset:]
