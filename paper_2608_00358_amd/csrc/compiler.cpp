@@ -1034,17 +1034,25 @@ namespace {
 
 // Tiles of a uniform phase, measured on MI355X with three sets of buffers in turn (so that a call
 // does not find its own inputs in the last-level cache). Bytes per tile are those of one source.
-//  * Reductions: 2 KiB, two vectors per lane and source; 4 KiB from 1 GiB moved on; 1 KiB for the
-//    binary tree, which takes one vector per lane. 1 / 2 / 4 KiB: 8-rank reduce-scatter of 64 MiB
-//    bf16 29.2 / 27.3 / 28.6 us, ragged 31.8 / 30.7 / 36.9, of 1 GiB 404 / 415 / 405; all-reduce
-//    of 8 x 16 MiB bf16 58.1 / 52.9 / 58.8; 16-rank halving reduce-scatter of 8 MiB fp16 23.9 /
-//    25.2 / 28.1. (8 and 16 KiB: the 1 GiB one 455 and 473 us.)
+//  * Reductions: 2 KiB, two vectors per lane and source; 1 KiB for the binary tree, which takes
+//    one vector per lane. 1 / 2 / 4 KiB: 8-rank reduce-scatter of 64 MiB bf16 29.2 / 27.3 / 28.6 us,
+//    ragged 31.8 / 30.7 / 36.9; all-reduce of 8 x 16 MiB bf16 58.1 / 52.9 / 58.8; 16-rank halving
+//    reduce-scatter of 8 MiB fp16 23.9 / 25.2 / 28.1.
+//  * From 1 GiB moved on, by the number of sources (1 / 2 / 4 KiB; the executor's kernel in brackets).
+//    Many of them, or some and one destination, 1 KiB: reduce-scatter of 8 ranks, 1.2 GiB moved bf16
+//    205 / 216 / 221 (234), of 8 x 256 MiB 406 / 415 / 412 (428), of 12 ranks, 1 GiB 175 / 184 / 190
+//    (176); all-reduce of 12 ranks, 1.2 GiB bf16 228 / 235 / 243 (232), of 15 231 / 244 / 269 (243);
+//    but reduce-scatter of 4, 1 GiB bf16 185 / 176 / 179 (196), of 2 223 / 168 / 168 (207). Two sources
+//    from 2 GiB on, 4 KiB: all-reduce bf16 of 2 GiB 405 / 368 / 343 (405), of 1 GiB 188 / 172 / 177
+//    (215). Others 2 KiB: all-reduce of 8 ranks, 1 GiB fp32 189 / 185 / 215 (218), 2 GiB bf16
+//    428 / 390 / 386 (366), 1.2 GiB bf16 220 / 226 / 233 (236). From 16 sources on 2 KiB again: of
+//    16 ranks, 1.2 GiB 225 / 228 / 233 (232).
 //  * Copies: 4 KiB. 2 / 4 / 8 KiB: all-gather of 8 x 8 MiB 95.5 / 86.4 / 97, of 2 x 64 MiB
 //    67.3 / 67.7 / 75.3, of 8 x 104 KB 6.1 / 5.1 / 5.4.
 //  * Small phases are cut further, down to one vector per lane, to give more wavefronts work.
 constexpr uint64_t kUniformReduceBytes = 2048;
-constexpr uint64_t kUniformLargeReduceBytes = 4096;
 constexpr uint64_t kUniformLargeMoved = 1ull << 30;
+constexpr uint32_t kUniformManySources = 9, kUniformSomeSources = 6;
 constexpr uint64_t kUniformCopyBytes = 4096;
 constexpr uint64_t kUniformCopyTiles = 256;
 constexpr uint64_t kUniformStepBytes = kWaveSize * 16;
@@ -1062,10 +1070,13 @@ constexpr uint32_t kUniformFewDsts = 4;
 constexpr uint64_t kUniformFewWaves = 16384;
 constexpr uint64_t kUniformWholeTiles = 1024;
 // A reduction that moves no more than this finds its inputs in the caches, where the producer left
-// them: ordinary loads (all-reduce of 8 x 64 KiB 6.0 -> 4.9 us back to back); beyond it the
-// non-temporal ones are as good or better (of 8 x 2 MiB 7.6 / 6.8, of 16 x 8 MiB 26.4 / 23.9, the
-// 1 GiB reduce-scatter 435 / 405). Results are stored non-temporally at every size (all-reduce of
-// 4 x 4 MiB: ordinary stores 7.8, non-temporal 6.9), unless a later phase of the program reads them.
+// them: ordinary loads (all-reduce of 8 x 64 KiB 6.0 -> 4.9 us back to back; maxima, trees and
+// re-quantised sums of 8 x 512 KiB alike, with either load 5.5, 4.4 and 4.7); beyond it the
+// non-temporal ones are as good or better (of 8 x 2 MiB 7.6 / 6.8, a maximum 7.5 / 7.2, of 16 x
+// 8 MiB 26.4 / 23.9, the 1 GiB reduce-scatter 435 / 405). Results are stored non-temporally at
+// every size (all-reduce of 4 x 4 MiB: ordinary stores 7.8, non-temporal 6.9; the reduce-scatter of
+// 8 x 256 MiB on buffers other than the last call's 418 / 405, called again on the same ones, whose
+// results the last-level cache then holds, 393 / 402), unless a later phase of the program reads them.
 constexpr uint64_t kUniformCachedBytes = 8ull << 20;
 
 // Copies of this many bytes to this many destinations stay on the executor's kernel where every
@@ -1088,8 +1099,13 @@ void uniform_tile(UniformPhase& u, uint64_t elems) {
     const uint64_t moved = elems * es * (u.nsrc() + u.ndst());
     uint64_t bytes = kUniformCopyBytes, sets = 1, want = kUniformCopyTiles;
     if (u.kernel.op == OP_REDUCE) {
-        bytes = u.kernel.fold == FOLD_PAIRWISE ? kUniformStepBytes
-              : moved >= kUniformLargeMoved && u.nsrc() < kSplitMinSources ? kUniformLargeReduceBytes : kUniformReduceBytes;
+        bytes = kUniformReduceBytes;
+        if (u.kernel.fold == FOLD_PAIRWISE) {
+            bytes = kUniformStepBytes;
+        } else if (moved >= kUniformLargeMoved && u.nsrc() < kSplitMinSources) {
+            if (u.nsrc() >= kUniformManySources || (u.nsrc() >= kUniformSomeSources && u.ndst() == 1)) bytes = kUniformStepBytes;
+            else if (u.nsrc() <= 2 && moved >= 2 * kUniformLargeMoved) bytes = 2 * kUniformReduceBytes;
+        }
         want = kSmallTargetTiles;
     } else {
         const uint64_t few = (u.ndst() + kUniformFewDsts - 1) / kUniformFewDsts;
