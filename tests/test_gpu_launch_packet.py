@@ -151,6 +151,11 @@ def test_in_place(fold, P, dt, op, cfg):
                     assert bufs[r].guards_intact()
 
 
+def to_host_floats(bits, dt):
+    t = torch.from_numpy(np.ascontiguousarray(bits).view(np.int16))
+    return t.view({"bf16": torch.bfloat16, "fp16": torch.float16}[dt]).to(torch.float32).numpy()
+
+
 def to_device_bits(v, dt):
     t = torch.from_numpy(v)
     if dt == "fp32":
@@ -173,6 +178,68 @@ def test_every_kind_of_value(op, order, requant, dt):
         oracle.allreduce_ordered(x, dt, order=order, shard=-(-(-(-n // P)) // 64) * 64, requant=requant)
     for r in range(P):
         assert same_bits(outs[r].result(), want[r], dt), first_mismatch(outs[r].result(), want[r])
+
+
+def test_bf16_rounding_of_every_sum():
+    """Every FP32 value that a sum of bf16 numbers can take (multiples of the smallest subnormal bf16,
+    2^-133), each as a sum of three: the result is rounded to nearest, ties to even."""
+    P, n = 3, 1 << 26
+    recv = [torch.empty(n, dtype=torch.bfloat16, device="cuda:0") for _ in range(P)]
+    with H.Comm(P, device=0) as c:
+        for k in range(1 << 6):
+            if k % 16 == 0:
+                print(f"bf16 rounding, patterns from {k << 26:#x}", flush=True)
+            u = torch.arange(k * n, (k + 1) * n, device="cuda:0") - (1 << 31)      # all patterns, as int64
+            x = u.to(torch.int32).view(torch.float32)
+            small = x.abs() < 2.0 ** -110                                          # below, drop the bits under 2^-133
+            x = torch.where(small, (x * 2.0 ** 120 * 2.0 ** 13).trunc() * 2.0 ** -120 * 2.0 ** -13, x)
+            x = torch.where(torch.isfinite(x), x, torch.zeros_like(x))
+            parts, rest = [], x
+            for _ in range(P):
+                top = (rest.view(torch.int32) & -65536).view(torch.float32)
+                parts.append((top.view(torch.int32) >> 16).to(torch.int16).view(torch.bfloat16))
+                rest = rest - top
+            assert not rest.any()
+            c.allreduce(parts, recv)
+            assert c.last_program()["inline_launch"] == 1
+            b = x.view(torch.int32).to(torch.int64) & 0xFFFFFFFF
+            want = ((b + 0x7FFF + ((b >> 16) & 1)) >> 16).to(torch.int16)
+            # (a sum that is zero is +0: the first part of -0 carries the sign and the others are +0)
+            want = torch.where(x == 0, torch.zeros_like(want), want)
+            for r in recv:
+                assert torch.equal(r.view(torch.int16), want)
+
+
+@pytest.mark.parametrize("dt", ["bf16", "fp16"])
+def test_vectors_and_single_elements_round_alike(dt):
+    """Infinities, NaNs of both kinds and signs, ties, overflow and subnormals, in pairs: the bits of a
+    call of whole vectors are those of calls of fewer elements than a vector, payload and sign of a
+    NaN included (which of two NaNs a sum keeps is not defined)."""
+    special = {"bf16": [0, 0x8000, 1, 0x8001, 0x7F, 0x80, 0x3F80, 0x3F81, 0xBF80, 0x3380, 0x3B80, 0x4380, 0x7F7F, 0xFF7F, 0x7E80, 0x7F80, 0xFF80,
+                        0x7F81, 0x7FC0, 0xFFC5, 0xFF81, 0x7FFF],
+               "fp16": [0, 0x8000, 1, 0x8001, 0x3FF, 0x400, 0x3C00, 0x3C01, 0xBC00, 0x1000, 0x0C00, 0x6400, 0x7BFF, 0xFBFF, 0x7000, 0x7C00, 0xFC00,
+                        0x7C01, 0x7E00, 0xFE05, 0xFC01, 0x7FFF]}[dt]
+    x = np.array([(a, b) for a in special for b in special], np.uint16).T.copy()
+    x = np.concatenate([x, np.zeros((2, -x.shape[1] % 56), np.uint16)], axis=1)   # whole vectors, and sevens
+    P, n = x.shape
+    with H.Comm(P, device=0) as c:
+        def run(lo, hi):
+            outs = [Guarded(hi - lo, dt) for _ in range(P)]
+            H.hccl_allreduce(c.handle, [to_device(x[r, lo:hi], dt) for r in range(P)], [o.view for o in outs], hi - lo, dt)
+            torch.cuda.synchronize()
+            assert c.last_program()["inline_launch"] == 1
+            return np.stack([o.result() for o in outs])
+
+        print(f"special values {dt}", flush=True)
+        whole = run(0, n)
+        single = np.concatenate([run(lo, lo + 7) for lo in range(0, n, 7)], axis=1)
+    nan = np.isnan(to_host_floats(x, dt))
+    one = ~(nan[0] & nan[1])
+    assert nan.any() and np.array_equal(whole[:, one], single[:, one]), first_mismatch(whole[0, one], single[0, one])
+    assert all(same_bits(a, b, dt) for a, b in zip(whole, single))
+    want = oracle.allreduce(x, dt)
+    for r in range(P):
+        assert same_bits(whole[r], want[r], dt), first_mismatch(whole[r], want[r])
 
 
 # ------------------------------------------------------------------ AllToAllvDynamic
