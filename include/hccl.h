@@ -20,8 +20,9 @@
  * the last failure. No call aborts or throws across this boundary.
  *
  * Limits: 1 <= nranks <= HCCL_MAX_RANKS. Element counts are in elements of `dtype`.
- * Buffers must be aligned to their element size; 16-byte aligned buffers take the
- * 128-bit vector path, other alignments a vector path with a head and tail of single
+ * Buffers must be aligned to their element size; 16-byte aligned buffers take the 128-bit
+ * vector path, other alignments the same path at the alignment of the elements in launches from
+ * packets and in exchanges; in the executor a vector path with a head and tail of single
  * elements where the destinations allow it, else element by element.
  *
  * Calls on one communicator must not run concurrently from several host threads. Calls
@@ -134,10 +135,11 @@ typedef enum { hcclPhasesAuto = 0, hcclPhasesOne = 1, hcclPhasesLevels = 2 } hcc
  * defaults.
  *
  * Two knobs of the paper have no field here. The message engines' cache-partition request
- * bits (Section II-A-3) keep collective buffers from evicting application data; the executor's
- * loads, and its copies' stores, always carry the non-temporal hint instead (the cache policy is
- * an instruction field fixed when the executor is compiled). Per-packet counters (Section V-C)
- * are the `trace` field.
+ * bits (Section II-A-3) keep collective buffers from evicting application data; here stores of
+ * results, and the loads of large aligned inputs, carry the non-temporal hint instead (the cache
+ * policy is an instruction field, fixed when a kernel is compiled; inputs that several
+ * wavefronts read, small reductions and loads at other alignments go without it). Per-packet
+ * counters (Section V-C) are the `trace` field.
  */
 typedef struct {
     int32_t algo;          /* hcclAlgo_t */
@@ -405,7 +407,8 @@ typedef struct {
     int32_t fused;               /* fusion pass applied */
     int32_t cache_hit;           /* 1 if the program came from the cache */
     uint32_t num_descs;          /* descriptors (steps) in the program */
-    uint32_t num_tiles;          /* work tickets */
+    uint32_t num_tiles;          /* tiles of the program image (work tickets); launches from their
+                                    packets and exchanges cut tiles of their own (see workers) */
     uint32_t num_deps;           /* dependency edges */
     uint32_t num_operands;       /* operand entries */
     uint32_t workers;            /* wavefronts of the last launch (0 on host-only comms) */
@@ -418,8 +421,8 @@ typedef struct {
     uint64_t scratch_bytes;      /* FP32 scratch the program needs */
     uint64_t program_bytes;      /* size of the device copy of the program */
     double compile_us;           /* host time to lower, fuse, validate and pack */
-    uint32_t step_tile_min;      /* smallest and largest tile (elements) of the program's copy and */
-    uint32_t step_tile_max;      /* reduce steps: steps of different element widths may differ */
+    uint32_t step_tile_min;      /* smallest and largest tile (elements) of the copy and reduce steps */
+    uint32_t step_tile_max;      /* in the image: steps of different element widths may differ */
     uint32_t num_phases;         /* executor launches per call (see hcclPhases_t) */
     uint32_t reserved;
 } hcclProgramInfo_t;
