@@ -408,7 +408,7 @@ hcclResult_t ensure_scratch(hcclComm* c, uint64_t bytes) {
     return hcclSuccess;
 }
 
-uint32_t stream_cu_count(hcclComm* c, hipStream_t s) {
+uint32_t stream_cu_count(const hcclComm* c, hipStream_t s) {
     if (!s) return (uint32_t)c->cus;
     uint32_t mask[16] = {0};
     if (hipExtStreamGetCUMask(s, 16, mask) != hipSuccess) return (uint32_t)c->cus;
@@ -632,11 +632,13 @@ hipError_t launch_uniform_phase(const hcclComm* c, const UniformPhase& u, char* 
     a.src_step = u.src_step;
     a.dst_step = u.dst_step;
     a.nseg = u.nseg;
-    a.tile_elems = u.tile_elems;
-    a.tiles_per_seg = (uint32_t)u.tiles_per_seg();
+    // (the mask of the stream is asked for only where it matters: reductions of a GiB and more)
+    const bool few_cus = u.few_cus_tile_elems != u.tile_elems && 4 * stream_cu_count(c, s) < 3 * (uint32_t)c->cus;
+    a.tile_elems = few_cus ? u.few_cus_tile_elems : u.tile_elems;
+    a.tiles_per_seg = (uint32_t)u.tiles_per_seg(a.tile_elems);
     const bool aligned = all_aligned(u, bufs);
     a.per_wave = aligned ? u.aligned_per_wave : u.per_wave;
-    a.ntiles = (uint32_t)u.ntiles(a.per_wave);
+    a.ntiles = (uint32_t)u.ntiles(a.tile_elems, a.per_wave);
     a.nsrc = u.nsrc();
     a.ndst = u.ndst();
     a.group = u.group;

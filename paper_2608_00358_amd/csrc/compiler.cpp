@@ -1046,7 +1046,10 @@ namespace {
 //    from 2 GiB on, 4 KiB: all-reduce bf16 of 2 GiB 405 / 368 / 343 (405), of 1 GiB 188 / 172 / 177
 //    (215). Others 2 KiB: all-reduce of 8 ranks, 1 GiB fp32 189 / 185 / 215 (218), 2 GiB bf16
 //    428 / 390 / 386 (366), 1.2 GiB bf16 220 / 226 / 233 (236). From 16 sources on 2 KiB again: of
-//    16 ranks, 1.2 GiB 225 / 228 / 233 (232).
+//    16 ranks, 1.2 GiB 225 / 228 / 233 (232). On a stream of few CUs what each of them has in flight
+//    counts: never 1 KiB there. 1 / 2 KiB: reduce-scatter of 8 x 256 MiB on 16 CUs 3 046 / 2 638 us
+//    (2 700), 64 829 / 746 (771), 128 488 / 468 (484), 192 387 / 399 (414), all-reduce of 12,
+//    1.5 GiB on 16 CUs 3 679 / 3 297 (3 581).
 //  * Copies: 4 KiB. 2 / 4 / 8 KiB: all-gather of 8 x 8 MiB 95.5 / 86.4 / 97, of 2 x 64 MiB
 //    67.3 / 67.7 / 75.3, of 8 x 104 KB 6.1 / 5.1 / 5.4.
 //  * Small phases are cut further, down to one vector per lane, to give more wavefronts work.
@@ -1118,7 +1121,9 @@ void uniform_tile(UniformPhase& u, uint64_t elems) {
         u.aligned_per_wave = resonant ? u.ndst() : u.per_wave;
     }
     while (bytes > kUniformStepBytes && elems * es / bytes * sets < want) bytes /= 2;
-    u.tile_elems = (uint32_t)(bytes / es);
+    u.tile_elems = u.few_cus_tile_elems = (uint32_t)(bytes / es);
+    if (u.kernel.op == OP_REDUCE && u.kernel.fold != FOLD_PAIRWISE && moved >= kUniformLargeMoved)
+        u.few_cus_tile_elems = (uint32_t)(std::max(bytes, kUniformReduceBytes) / es);
 }
 
 bool same_bufs(const std::vector<Operand>& a, const std::vector<Operand>& b) {
@@ -1342,10 +1347,10 @@ UniformPhase find_uniform(const std::vector<HostDesc>& all, uint32_t d0, uint32_
     if (f.op == OP_REDUCE && reread) u.kernel.mem = MEM_STORE;
     else if (f.op == OP_REDUCE && total * es * (u.nsrc() + u.ndst()) <= kUniformCachedBytes) u.kernel.mem = MEM_LOAD;
     u.per_wave = u.aligned_per_wave = 1;
-    if (tile) u.tile_elems = tile;
+    if (tile) u.tile_elems = u.few_cus_tile_elems = tile;
     else uniform_tile(u, total);
     u.long_run = f.op == OP_COPY && u.ndst() >= kLongRunDsts && total * es >= kLongRunBytes;
-    u.ok = u.ntiles(u.per_wave) < (1ull << 31) && !one_long_copy(f.op, u.nseg, u.ndst(), total * es);
+    u.ok = u.ntiles(u.tile_elems, u.per_wave) < (1ull << 31) && !one_long_copy(f.op, u.nseg, u.ndst(), total * es);
     return u;
 }
 

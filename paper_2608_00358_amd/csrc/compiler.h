@@ -92,14 +92,15 @@ struct UniformPhase {
     uint64_t src_step = 0, dst_step = 0;  // bytes
     uint32_t flags = 0;                   // UF_SRC_PER_SEG, UF_DST_PER_SEG, UF_ROTATE, UF_XCD
     uint32_t tile_elems = 0;
+    uint32_t few_cus_tile_elems = 0;      // ... on a stream of few of the CUs
     uint32_t per_wave = 0;                // copies: destinations of one wavefront; ...
     uint32_t aligned_per_wave = 0;        // ... where every operand is 16-byte aligned
     std::vector<Operand> srcs, dsts;      // of segment 0, or one per segment
     uint32_t nsrc() const { return flags & UF_SRC_PER_SEG ? 1u : (uint32_t)srcs.size(); }
     uint32_t ndst() const { return flags & UF_DST_PER_SEG ? 1u : (uint32_t)dsts.size(); }
-    uint64_t tiles_per_seg() const { return (seg_elems + tile_elems - 1) / tile_elems; }
-    uint64_t ntiles(uint32_t per_wave) const {
-        const uint64_t t = (nseg - 1) * tiles_per_seg() + (last_elems + tile_elems - 1) / tile_elems;
+    uint64_t tiles_per_seg(uint32_t tile) const { return (seg_elems + tile - 1) / tile; }
+    uint64_t ntiles(uint32_t tile, uint32_t per_wave) const {
+        const uint64_t t = (nseg - 1) * tiles_per_seg(tile) + (last_elems + tile - 1) / tile;
         return kernel.op == OP_COPY ? t * ((ndst() + per_wave - 1) / per_wave) : t;
     }
 };

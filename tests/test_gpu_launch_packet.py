@@ -7,7 +7,7 @@ import torch
 
 import oracle
 import paper_2608_00358_amd as H
-from gpu_helpers import Guarded, first_mismatch, same_bits, to_device
+from gpu_helpers import Guarded, MaskedStream, first_mismatch, same_bits, to_device
 from test_gpu_dynamic import random_counts, run_dynamic
 from test_gpu_orders import lib_shard, run_ar, run_rs
 from test_gpu_parity import inputs, run_allgather, run_allreduce, run_reduce_scatter
@@ -178,6 +178,31 @@ def test_every_kind_of_value(op, order, requant, dt):
         oracle.allreduce_ordered(x, dt, order=order, shard=-(-(-(-n // P)) // 64) * 64, requant=requant)
     for r in range(P):
         assert same_bits(outs[r].result(), want[r], dt), first_mismatch(outs[r].result(), want[r])
+
+
+def test_large_reductions_on_few_cus():
+    """From 1 GiB moved on the tiles depend on the CUs of the stream, the results do not."""
+    for P, n in ((8, (1 << 23) + 5), (12, 4 << 20)):
+        g = torch.Generator(device="cuda:0").manual_seed(P)
+        send = [torch.randn(P * n, generator=g, device="cuda:0").to(torch.bfloat16) for _ in range(P)]
+        want = send[0].float()
+        for s in send[1:]:
+            want += s
+        want = want.to(torch.bfloat16).view(P, n)
+        torch.cuda.synchronize()
+        workers = []
+        with MaskedStream(2) as few, H.Comm(P, device=0) as c:
+            for stream in (None, few):
+                print(f"reduce-scatter P={P} n={n} on {'16 CUs' if stream else 'all CUs'}", flush=True)
+                out = [Guarded(n, "bf16") for _ in range(P)]
+                torch.cuda.synchronize()
+                H.hccl_reduce_scatter(c.handle, send, [o.view for o in out], n, "bf16", stream=stream)
+                torch.cuda.synchronize()
+                workers.append(c.last_program()["workers"])
+                assert c.last_program()["inline_launch"] == 1
+                for r in range(P):
+                    assert torch.equal(out[r].view, want[r]) and out[r].guards_intact()
+        assert workers[1] < workers[0]
 
 
 def test_bf16_rounding_of_every_sum():
