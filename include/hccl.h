@@ -434,7 +434,8 @@ hcclResult_t hccl_comm_last_program(hcclComm_t comm, hcclProgramInfo_t* info);
  * description of the work packet, its WQEs and their dependency metadata, before the device
  * runs it), exactly as uploaded: a header, then 64-byte steps, 16-byte operands {buffer id,
  * element type, byte offset}, 16-byte dependencies {step, kind, expected count, state word},
- * one owning step per tile and the AllToAllvDynamic records (layout: csrc/program.h). Buffer
+ * one owning step per tile, the AllToAllvDynamic records, the phase table and, for exchanges, the
+ * copy list their launches read (layout: csrc/program.h). Buffer
  * ids, not addresses, name the operands: send buffers 0..P-1, receive buffers P..2P-1, the
  * scratch 2P (in a group, each call's ids follow the previous calls'). For tools and tests,
  * e.g. an interpreter that runs the steps in any order the dependencies allow. Copies
